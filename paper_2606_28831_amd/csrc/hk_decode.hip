@@ -250,144 +250,100 @@ __global__ __launch_bounds__(DEC_NT) void decode_split_kernel(
   }
 }
 
-// One workgroup per KV head merges the split states of its G query heads (App. F).  A
-// 32-lane group per query head loads the (m, l) of up to DEC_MRG_CACHE splits once into
-// registers, finds the running maximum M and the rescaled sum L from them, and leaves each
-// split's factor exp2(m - M) in LDS; then each (query head, dim) thread sums its split
-// outputs times those factors.  Only the splits that held pages of the row count (none for
-// an empty row, which gives o = 0, lse = -inf).  When the launch has at most
-// DEC_MRG_SPEC splits, every load -- the row's page count, the split states, the thread's
-// split outputs -- is issued at once, before the count of splits that held pages is known,
-// and the states of the others are dropped unread (their memory holds an earlier call's
-// values); otherwise the outputs are loaded after the factors, and rows with more splits
-// than the register cache read the rest from memory.
-constexpr int DEC_MRG_CACHE = 128;            // splits per query head kept in registers / LDS
-constexpr int DEC_MRG_SPEC = 8;               // splits loaded before the split count is known
-template <int D>
-__global__ __launch_bounds__(256) void decode_merge_kernel(const float* __restrict__ part,
-                                                           const int32_t* __restrict__ n_pages_arr,
-                                                           int max_pages, int n_split_all, int pps,
-                                                           int G, int Hq, int Hkv, float* __restrict__ o,
-                                                           float* __restrict__ lse) {
-  constexpr int KPL = DEC_MRG_CACHE / 32;     // cached splits per lane
-  constexpr int OPT = 8 * D / 256;            // outputs per thread at the largest group (8)
-  __shared__ float s_M[8], s_L[8];
-  __shared__ float s_a[8][DEC_MRG_CACHE];
-  const int h = blockIdx.x, s = h / Hkv, kv = h % Hkv;
+// NW waves per query head merge its split states (App. F).  Lanes hold two output columns
+// each, and a group of D / 2 lanes takes every NG-th split, U of them in flight at once, so
+// the chain of dependent loads is n_split / (NG * U) long.  Every wave reads all (m, l) itself (64 splits per load) for the running
+// maximum M and the rescaled sum L; a split's own factor exp2(m - M) comes from the m loaded
+// beside its outputs.  The first batch of loads -- page count, states and outputs -- is issued
+// before the number of splits that held pages is known; the states of the others are dropped
+// unread (their memory holds an earlier call's values).  Launches of at most 8 splits take
+// one wave per query head, which then has every split in flight; more splits take four
+// waves.  Bound by the latency of two or three dependent loads: 16 heads x 7 query heads x
+// 128 splits 45.6 -> 5.5 us against one workgroup per KV head with four loads in flight per
+// thread, 8 heads x 4 x 48 splits 5.7 -> 3.2 us, 512 heads x 4 x 6 splits 6.3 -> 5.3 us.
+constexpr int MRG_NT = 256;
+template <int D, int NW, int U>
+__global__ __launch_bounds__(MRG_NT) void decode_merge_kernel(const float* __restrict__ part,
+                                                              const int32_t* __restrict__ n_pages_arr,
+                                                              int max_pages, int n_split_all, int pps,
+                                                              int n_q, int G, int Hq, int Hkv,
+                                                              float* __restrict__ o,
+                                                              float* __restrict__ lse) {
+  constexpr int LPS = D / 2;                  // lanes per split, two columns each
+  constexpr int TPQ = 64 * NW;                // threads per query head
+  constexpr int NG = TPQ / LPS;               // lane groups
+  __shared__ float2 s_o[MRG_NT / TPQ][NG][LPS];
+  const int qi = threadIdx.x / TPQ, tq = threadIdx.x % TPQ;
+  // past the last query head: the last one again, not stored
+  const int q_row = (int)blockIdx.x * (MRG_NT / TPQ) + qi, q_cl = min(q_row, n_q - 1);
+  const int h = q_cl / G, g = q_cl % G;
+  const int s = h / Hkv, kv = h % Hkv;
+  const int lane = threadIdx.x & 63, grp = tq / LPS, col = tq % LPS;
   const size_t stride = (size_t)G * (D + 2);
-  const float* base = part + (size_t)h * n_split_all * stride;
-  const bool spec = n_split_all <= DEC_MRG_SPEC;
+  const float* base = part + (size_t)h * n_split_all * stride + (size_t)g * (D + 2);
   const int n = min(n_pages_arr[h], max_pages);
-  const int g = threadIdx.x >> 5, l32 = threadIdx.x & 31;
-  const float* pg = base + g * (D + 2);
-  // split states (speculatively up to n_split_all when spec) and the thread's split outputs
-  const int n_load = spec ? n_split_all : 0;
-  float mv[KPL], lv[KPL];
+  // (m, l) of the splits lane and lane + 64; outputs and m of the splits grp + NG * (j0 + u),
+  // clamped to the launch's last split
+  auto load_ml = [&](int i) {
+    return i < n_split_all ? *reinterpret_cast<const float2*>(base + i * stride + D) : make_float2(-INFINITY, 0.f);
+  };
+  float2 ml0 = load_ml(lane), ml1 = load_ml(lane + 64);
+  float2 ov[U];
+  float mv[U];
+  auto load_o = [&](int j0) {
 #pragma unroll
-  for (int k = 0; k < KPL; ++k) {
-    const int i = l32 + 32 * k;
-    mv[k] = -INFINITY;
-    lv[k] = 0.f;
-    if (g < G && i < n_load) {
-      mv[k] = pg[i * stride + D];
-      lv[k] = pg[i * stride + D + 1];
+    for (int u = 0; u < U; ++u) {
+      const int i = min(grp + NG * (j0 + u), n_split_all - 1);
+      const float* p = base + i * stride;
+      ov[u] = *reinterpret_cast<const float2*>(p + 2 * col);
+      mv[u] = p[D];
     }
-  }
-  float ov[OPT][DEC_MRG_SPEC];
-  if (spec) {
-#pragma unroll
-    for (int q = 0; q < OPT; ++q) {
-      const int idx = threadIdx.x + 256 * q;
-      const int gq = idx / D, d = idx % D;
-#pragma unroll
-      for (int i = 0; i < DEC_MRG_SPEC; ++i)
-        ov[q][i] = (idx < G * D && i < n_split_all) ? base[i * stride + gq * (D + 2) + d] : 0.f;
-    }
-  }
+  };
+  load_o(0);
   const int share = decode_share(n, n_split_all, pps);
   const int n_split = n > 0 ? min(n_split_all, (n + share - 1) / share) : 0;
-  {
-    float M = -INFINITY, L = 0.f;
-#pragma unroll
-    for (int k = 0; k < KPL; ++k) {
-      const int i = l32 + 32 * k;
-      if (g < G && i < n_split && !spec) {
-        mv[k] = pg[i * stride + D];
-        lv[k] = pg[i * stride + D + 1];
-      }
-      if (i >= n_split) {                       // a split that held no pages of this row
-        mv[k] = -INFINITY;
-        lv[k] = 0.f;
-      }
-      M = fmaxf(M, mv[k]);
+  if (lane >= n_split) ml0 = make_float2(-INFINITY, 0.f);
+  if (lane + 64 >= n_split) ml1 = make_float2(-INFINITY, 0.f);
+  float M = fmaxf(ml0.x, ml1.x);
+  for (int i = lane + 128; i < n_split; i += 64) M = fmaxf(M, base[i * stride + D]);
+  M = wave_max(M);
+  float L = 0.f;
+  float2 acc = make_float2(0.f, 0.f);
+  if (M != -INFINITY) {                       // the same in every wave
+    if (lane < n_split) L += ml0.y * exp2f(ml0.x - M);
+    if (lane + 64 < n_split) L += ml1.y * exp2f(ml1.x - M);
+    for (int i = lane + 128; i < n_split; i += 64) {
+      const float2 ml = *reinterpret_cast<const float2*>(base + i * stride + D);
+      L += ml.y * exp2f(ml.x - M);
     }
-    if (g < G)
-      for (int i = l32 + DEC_MRG_CACHE; i < n_split; i += 32) M = fmaxf(M, pg[i * stride + D]);
+    L = wave_sum(L);
+    for (int j0 = 0;;) {
 #pragma unroll
-    for (int x = 1; x < 32; x <<= 1) M = fmaxf(M, __shfl_xor(M, x, 32));
-    if (g < G && M != -INFINITY) {
-#pragma unroll
-      for (int k = 0; k < KPL; ++k) {
-        const float a = exp2f(mv[k] - M);         // 0 for a split past n_split
-        L += lv[k] * a;
-        s_a[g][l32 + 32 * k] = a;
-      }
-      for (int i = l32 + DEC_MRG_CACHE; i < n_split; i += 32) {
-        const float* p = pg + i * stride;
-        L += p[D + 1] * exp2f(p[D] - M);
-      }
-    }
-#pragma unroll
-    for (int x = 1; x < 32; x <<= 1) L += __shfl_xor(L, x, 32);
-    if (g < G && l32 == 0) {
-      s_M[g] = M;
-      s_L[g] = L;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < OPT; ++q) {
-    const int idx = threadIdx.x + 256 * q;
-    if (idx >= G * D) break;
-    const int gq = idx / D, d = idx % D;
-    const float M = s_M[gq], L = s_L[gq];
-    const float* p = base + gq * (D + 2);
-    const float* a = s_a[gq];
-    float O0 = 0.f, O1 = 0.f, O2 = 0.f, O3 = 0.f;
-    if (M != -INFINITY) {
-      if (spec) {
-        // the same grouping as below: fours into O0..O3, the rest into O0, slot order
-#pragma unroll
-        for (int i = 0; i + 4 <= DEC_MRG_SPEC; i += 4)
-          if (i + 4 <= n_split) {
-            O0 = fmaf(ov[q][i], a[i], O0);
-            O1 = fmaf(ov[q][i + 1], a[i + 1], O1);
-            O2 = fmaf(ov[q][i + 2], a[i + 2], O2);
-            O3 = fmaf(ov[q][i + 3], a[i + 3], O3);
-          }
-#pragma unroll
-        for (int i = 0; i < DEC_MRG_SPEC; ++i)
-          if (i >= (n_split & ~3) && i < n_split) O0 = fmaf(ov[q][i], a[i], O0);
-      } else {
-        const int nc = min(n_split, DEC_MRG_CACHE);
-        int i = 0;
-        for (; i + 4 <= nc; i += 4) {
-          const float* q0 = p + i * stride;
-          const float v0 = q0[d], v1 = q0[stride + d], v2 = q0[2 * stride + d], v3 = q0[3 * stride + d];
-          O0 = fmaf(v0, a[i], O0);
-          O1 = fmaf(v1, a[i + 1], O1);
-          O2 = fmaf(v2, a[i + 2], O2);
-          O3 = fmaf(v3, a[i + 3], O3);
+      for (int u = 0; u < U; ++u)
+        if (grp + NG * (j0 + u) < n_split) {
+          const float a = exp2f(mv[u] - M);
+          acc.x = fmaf(ov[u].x, a, acc.x);
+          acc.y = fmaf(ov[u].y, a, acc.y);
         }
-        for (; i < nc; ++i) O0 = fmaf(p[i * stride + d], a[i], O0);
-        for (; i < n_split; ++i) O0 = fmaf(p[i * stride + d], exp2f(p[i * stride + D] - M), O0);
-      }
+      j0 += U;
+      if (NG * j0 >= n_split) break;
+      load_o(j0);
     }
-    const float O = (O0 + O1) + (O2 + O3);
-    const size_t row = (size_t)s * Hq + kv * G + gq;
-    o[row * D + d] = (L > 0.f) ? O / L : 0.f;
-    if (d == 0) lse[row] = (L > 0.f) ? (M + __log2f(L)) * kLn2 : -INFINITY;
   }
+  s_o[qi][grp][col] = acc;
+  __syncthreads();
+  const size_t row = (size_t)s * Hq + kv * G + g;
+  if (tq < LPS && q_row < n_q) {
+    float2 t = s_o[qi][0][col];
+#pragma unroll
+    for (int q = 1; q < NG; ++q) {
+      t.x += s_o[qi][q][col].x;
+      t.y += s_o[qi][q][col].y;
+    }
+    o[row * D + 2 * col] = L > 0.f ? t.x / L : 0.f;        // (o need not be 8-byte aligned)
+    o[row * D + 2 * col + 1] = L > 0.f ? t.y / L : 0.f;
+  }
+  if (tq == 0 && q_row < n_q) lse[row] = (L > 0.f) ? (M + __log2f(L)) * kLn2 : -INFINITY;
 }
 
 // ------------------------------------------------------------------ a6: append
@@ -582,12 +538,18 @@ hipError_t hk_launch_decode(int NS, int Hq, int Hkv, int D, const void* q, const
   }
   if (!ok) return hipErrorInvalidValue;
   TimedLaunch t(timed ? HK_TK_DECODE_MERGE : -1, st);
-  if (D == 128)
-    hipLaunchKernelGGL(decode_merge_kernel<128>, dim3(n_heads), dim3(256), 0, st, part, kv->n_pages,
-                       kv->max_pages, n_split, pps, G, Hq, Hkv, o, lse);
-  else
-    hipLaunchKernelGGL(decode_merge_kernel<64>, dim3(n_heads), dim3(256), 0, st, part, kv->n_pages,
-                       kv->max_pages, n_split, pps, G, Hq, Hkv, o, lse);
+  const int n_q = n_heads * G;
+#define HK_MERGE(D_, NW_, U_)                                                                      \
+  hipLaunchKernelGGL((decode_merge_kernel<D_, NW_, U_>), dim3((n_q * NW_ + 3) / 4), dim3(MRG_NT), 0, \
+                     st, part, kv->n_pages, kv->max_pages, n_split, pps, n_q, G, Hq, Hkv, o, lse)
+  if (D == 128) {
+    if (n_split <= 8) HK_MERGE(128, 1, 8);
+    else HK_MERGE(128, 4, 8);
+  } else {
+    if (n_split <= 8) HK_MERGE(64, 1, 4);
+    else HK_MERGE(64, 4, 8);
+  }
+#undef HK_MERGE
   return hipGetLastError();
 }
 
