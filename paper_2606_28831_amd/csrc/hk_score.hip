@@ -23,6 +23,7 @@
 // either the A or the B operand.
 // Accumulator layout of the 32x32 MFMA: register r of lane l holds row
 // 8*(r/4) + 4*(l/32) + (r%4), column l % 32.
+#include <algorithm>
 #include <type_traits>
 
 #include "hk_internal.h"
@@ -147,7 +148,10 @@ __device__ __forceinline__ void stage_rows(char* lds, int R, int R_pad, RowFn ro
 constexpr int SCORE_NT = 512;              // threads per workgroup
 constexpr int SCORE_QD = 2;                // Q fragments read from LDS this many MFMA steps ahead
 constexpr int SCORE_NW = SCORE_NT / 64;
-constexpr int SCORE_PPW = 128;             // pages per workgroup
+constexpr int SCORE_PPW = 128;             // most pages per workgroup
+constexpr int SCORE_PPW_MIN = 16;          // fewest: one 32-key tile per wave
+constexpr int SCORE_TARGET_WG = 256;       // workgroups a pass should offer: one per CU
+constexpr int SCORE_MAX_PARTS = 4096;      // most workgroups a launch with shorter chunks takes
 constexpr int SCORE_KT = 1;                // 32-key tiles a wave holds at once
 constexpr int SCORE_WPP = 2 * SCORE_KT;    // pages per wave iteration
 constexpr int NREF_MAX = 256;
@@ -158,6 +162,42 @@ __host__ __device__ constexpr int qb_eff(int qb) {
   return qb <= 1 ? 1 : qb <= 2 ? 2 : qb <= 4 ? 4 : qb <= 7 ? 7 : 8;
 }
 __host__ __device__ constexpr int score_rpad(int R) { return 32 * qb_eff((R + 31) / 32); }
+
+// Pages per workgroup (a chunk) of a launch over n_heads rows of max_pages pages.  A chunk
+// pays for its query block, page ids and first tiles before it computes.  A launch whose
+// workgroups share a CU two by two (the bf16 passes) takes the longest chunks that still give
+// it SCORE_TARGET_WG workgroups, one per CU: both passes and the merge, chunks of 128 pages ->
+// this rule: 8 heads x 512 pages 61 -> 26 us (16 pages), 8 x 2048 63 -> 46 (64; 32 pages 53,
+// 16 pages 78), 200 x 128 at G 7 88 -> 81 (64), 32 x 1024 stays at 128 (70; 64 pages 71, 32
+// pages 91).  Never more than SCORE_MAX_PARTS workgroups by shorter chunks (workspace).
+static int score_ppw(int n_heads, int max_pages) {
+  int p = SCORE_PPW;
+  while (p > SCORE_PPW_MIN && (long long)n_heads * ((max_pages + p - 1) / p) < SCORE_TARGET_WG) p >>= 1;
+  return p;
+}
+// The same where one workgroup fills a CU (fp32, and the redundancy pass): the launch then
+// runs in rounds of one workgroup per CU, each as long as a chunk and its set-up (in pages'
+// time), so 200 workgroups beat 400 half as long.  fp32: 2 heads x 128 pages 150 -> 30 us (16
+// pages), 64 x 256 296 -> 164 (64), 160 x 128 295 -> 279 (32), 200 x 128 stays at 128 (296; 64
+// pages 302).  Redundancy pass (set-up 48: it stages every reference row; whole score call,
+// 512 pages -> this rule): 8 heads x 1024 pages 194 -> 41 us, 32 x 1024 211 -> 98, 64 x 1024
+// 235 -> 176.
+static int score_ppw_rounds(int n_heads, int max_pages, int most, int least, int setup) {
+  int best = most;
+  long long cost = -1;
+  for (int p = most; p >= least; p >>= 1) {
+    const long long wg = (long long)n_heads * ((max_pages + p - 1) / p);
+    if (p < most && wg > SCORE_MAX_PARTS) break;
+    const long long c = (wg + SCORE_TARGET_WG - 1) / SCORE_TARGET_WG * (std::min(p, max_pages) + setup);
+    if (cost < 0 || c < cost) best = p, cost = c;
+  }
+  return best;
+}
+template <typename T>
+static int score_ppw_t(int n_heads, int max_pages) {
+  return sizeof(T) == 2 ? score_ppw(n_heads, max_pages)
+                        : score_ppw_rounds(n_heads, max_pages, SCORE_PPW, SCORE_PPW_MIN, 8);
+}
 
 // MFMA chain of one 32x32 output block over the whole head dimension.  LDS_IS_A: the
 // LDS block is the A operand (rows of C), the register fragment the B operand.
@@ -466,7 +506,7 @@ template <typename T, int D, int QB>
 __global__ __launch_bounds__(SCORE_NT) void score_pass1_kernel(
     const T* __restrict__ q_obs, const T* __restrict__ k_pool, const int32_t* __restrict__ table,
     const uint16_t* __restrict__ masks, const int32_t* __restrict__ n_pages_arr, int NS, int Hq,
-    int Hkv, int W, int max_pages, float c2, float2* __restrict__ part, int n_chunks) {
+    int Hkv, int W, int max_pages, float c2, float2* __restrict__ part, int n_chunks, int ppw) {
   using F = Frag<T, D>;
   constexpr int R_pad = 32 * QB;
   extern __shared__ __align__(16) char smem[];
@@ -483,7 +523,7 @@ __global__ __launch_bounds__(SCORE_NT) void score_pass1_kernel(
   __syncthreads();
 
   const int n = n_pages_arr[h];
-  const int p_begin = chunk * SCORE_PPW, p_end = min(p_begin + SCORE_PPW, n);
+  const int p_begin = chunk * ppw, p_end = min(p_begin + ppw, n);
   float M[QB], L[QB];
 #pragma unroll
   for (int q = 0; q < QB; ++q) { M[q] = -INFINITY; L[q] = 0.f; }
@@ -628,11 +668,11 @@ void score_pass2_kernel(
     const uint16_t* __restrict__ masks, const int32_t* __restrict__ n_pages_arr, int NS, int Hq,
     int Hkv, int W, int max_pages, int L_dense, float c2, float lnR,
     const float* __restrict__ row_lse, float* __restrict__ s_out, int32_t* __restrict__ cand_len_out,
-    const int32_t* __restrict__ ref_slots, int n_ref, float* __restrict__ x_red) {
+    const int32_t* __restrict__ ref_slots, int n_ref, float* __restrict__ x_red, int ppw) {
   using F = Frag<T, D>;
   constexpr int R_pad = 32 * QB;
   extern __shared__ __align__(16) char smem[];
-  constexpr int NT = P2Shape<RED>::NT, NW = NT / 64, PPW = P2Shape<RED>::PPW;
+  constexpr int NT = P2Shape<RED>::NT, NW = NT / 64;
   const int h = blockIdx.y, chunk = blockIdx.x;
   const int s = h / Hkv, kv = h % Hkv, G = Hq / Hkv;
   const int R = G * W;
@@ -644,7 +684,7 @@ void score_pass2_kernel(
 
   const int32_t* trow = table + (size_t)h * max_pages;
   const uint16_t* mrow = masks + (size_t)h * max_pages;
-  const int p_begin = chunk * PPW, p_end_all = min(p_begin + PPW, max_pages);
+  const int p_begin = chunk * ppw, p_end_all = min(p_begin + ppw, max_pages);
   const int p_cand_end = min(p_end_all, cand_len / HK_PAGE);
 
   // slots of this chunk that hold no candidate: -inf
@@ -681,7 +721,7 @@ void score_pass2_kernel(
     RB = nr_pad >> 5;
     rn_ref = reinterpret_cast<float*>(ref_lds + (size_t)NREF_MAX * D * sizeof(T));
     ref_slot = reinterpret_cast<int32_t*>(rn_ref + NREF_MAX);
-    ref_bits = reinterpret_cast<uint32_t*>(ref_slot + NREF_MAX);   // [PPW / 2] words
+    ref_bits = reinterpret_cast<uint32_t*>(ref_slot + NREF_MAX);   // [ppw / 2] words
     const int32_t* rs = ref_slots + (size_t)h * n_ref;
     auto ref_row = [&](int i) -> const T* {
       const int j = rs[i];
@@ -692,7 +732,7 @@ void score_pass2_kernel(
     // padding rows (n_ref <= i < nr_pad) repeat reference 0: a repeated member changes
     // neither the maximum nor the self test (its slot is reference 0's)
     stage_rows<T, D>(ref_lds, nr_pad, nr_pad, [&](int i) { return ref_row(i < n_ref ? i : 0); });
-    for (int i = threadIdx.x; i < PPW / 2; i += NT) ref_bits[i] = 0u;
+    for (int i = threadIdx.x; i < ppw / 2; i += NT) ref_bits[i] = 0u;
     __syncthreads();
     for (int i = threadIdx.x; i < nr_pad; i += NT) {
       // squared norm of reference row i, read back from its fragment-major LDS image
@@ -723,7 +763,7 @@ void score_pass2_kernel(
       const int slot = rs[i < n_ref ? i : 0];
       ref_slot[i] = slot;
       const int rel = slot - p_begin * HK_PAGE;    // reference slots inside this chunk
-      if (i < n_ref && rel >= 0 && rel < PPW * HK_PAGE)
+      if (i < n_ref && rel >= 0 && rel < ppw * HK_PAGE)
         atomicOr(&ref_bits[rel >> 5], 1u << (rel & 31));
     }
   }
@@ -800,7 +840,7 @@ struct Coop {
   static constexpr int LPT = (ITER_CH + NT - 1) / NT;   // pieces each thread loads per iteration
   static constexpr int STAGES = 4;                      // iterations loaded ahead (4: unrolled)
   static constexpr int PPI = 2 * TPI;                   // pages per iteration
-  static constexpr int PPW = 128;                       // pages per workgroup
+  static constexpr int PPW = SCORE_PPW;                 // most pages per workgroup
   static constexpr int BUF = ITER_CH * 16;              // bytes of one LDS tile buffer
   static constexpr int ACTIVE = TPI * QB < NW ? TPI * QB : NW;   // waves with a query block
   static_assert(STAGES == 4, "the main loop is written out for four stages");
@@ -887,14 +927,15 @@ __device__ __forceinline__ void coop_store(const u32x4 (&r)[N], char* buf) {
 // The chunk's page ids and masks into LDS; the wave's query block as an MFMA fragment.
 template <int D, int QB, int KS>
 __device__ __forceinline__ void coop_setup(char* smem, const int32_t* trow, const uint16_t* mrow,
-                                           int p_begin, int p_stage_end, const uint16_t* __restrict__ q_obs,
+                                           int p_begin, int p_stage_end, int ppw,
+                                           const uint16_t* __restrict__ q_obs,
                                            int NS, int Hq, int Hkv, int W, int s, int kv, int qb, bool active,
                                            bf16x8 (&qf)[KS]) {
   using C = Coop<D, QB>;
   using L = CoopLds<D, QB>;
   int32_t* s_table = reinterpret_cast<int32_t*>(smem + L::TABLE);
   uint32_t* s_mask = reinterpret_cast<uint32_t*>(smem + L::MASK);
-  for (int i = threadIdx.x; i < C::PPW; i += C::NT) {
+  for (int i = threadIdx.x; i < ppw; i += C::NT) {
     const int pg = p_begin + i;
     s_table[i] = pg < p_stage_end ? trow[pg] : 0;
     s_mask[i] = pg < p_stage_end ? (uint32_t)mrow[pg] : 0u;
@@ -918,7 +959,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void score_pass1_coop_kernel(const uint16_t* __restrict__ q_obs, const uint16_t* __restrict__ k_pool,
                              const int32_t* __restrict__ table, const uint16_t* __restrict__ masks,
                              const int32_t* __restrict__ n_pages_arr, int NS, int Hq, int Hkv, int W,
-                             int max_pages, float c2, float2* __restrict__ part, int n_chunks) {
+                             int max_pages, float c2, float2* __restrict__ part, int n_chunks, int ppw) {
   using C = Coop<D, QB>;
   using L = CoopLds<D, QB>;
   constexpr int R_pad = 32 * QB;
@@ -929,9 +970,9 @@ void score_pass1_coop_kernel(const uint16_t* __restrict__ q_obs, const uint16_t*
   const bool active = wave < C::ACTIVE;
   const int ts = wave / QB, qb = wave % QB;
   const int n = n_pages_arr[h];
-  const int p_begin = chunk * C::PPW, p_end = min(p_begin + C::PPW, n);
+  const int p_begin = chunk * ppw, p_end = min(p_begin + ppw, n);
   bf16x8 qf[C::KS];
-  coop_setup<D, QB>(smem, table + (size_t)h * max_pages, masks + (size_t)h * max_pages, p_begin, p_end,
+  coop_setup<D, QB>(smem, table + (size_t)h * max_pages, masks + (size_t)h * max_pages, p_begin, p_end, ppw,
                     q_obs, NS, Hq, Hkv, W, s, kv, qb, active, qf);
   const int32_t* s_table = reinterpret_cast<const int32_t*>(smem + L::TABLE);
   const uint32_t* s_mask = reinterpret_cast<const uint32_t*>(smem + L::MASK);
@@ -1096,7 +1137,7 @@ void score_pass2_coop_kernel(const uint16_t* __restrict__ q_obs, const uint16_t*
                              const int32_t* __restrict__ n_pages_arr, int NS, int Hq, int Hkv, int W,
                              int max_pages, int L_dense, float c2, float lnR,
                              const float* __restrict__ row_lse, float* __restrict__ s_out,
-                             int32_t* __restrict__ cand_len_out) {
+                             int32_t* __restrict__ cand_len_out, int ppw) {
   using C = Coop<D, QB>;
   using L = CoopLds<D, QB>;
   extern __shared__ __align__(16) char smem[];
@@ -1110,7 +1151,7 @@ void score_pass2_coop_kernel(const uint16_t* __restrict__ q_obs, const uint16_t*
   const int n = n_pages_arr[h];
   const int cand_len = HK_PAGE * max(0, n - dense_pages(L_dense));
   if (chunk == 0 && threadIdx.x == 0) cand_len_out[h] = cand_len;
-  const int p_begin = chunk * C::PPW, p_end_all = min(p_begin + C::PPW, max_pages);
+  const int p_begin = chunk * ppw, p_end_all = min(p_begin + ppw, max_pages);
   const int p_cand_end = min(p_end_all, cand_len / HK_PAGE);
   float* srow = s_out + (size_t)h * S_max;
   {
@@ -1121,7 +1162,7 @@ void score_pass2_coop_kernel(const uint16_t* __restrict__ q_obs, const uint16_t*
   if (p_begin >= p_cand_end) return;
 
   bf16x8 qf[C::KS];
-  coop_setup<D, QB>(smem, table + (size_t)h * max_pages, masks + (size_t)h * max_pages, p_begin, p_cand_end,
+  coop_setup<D, QB>(smem, table + (size_t)h * max_pages, masks + (size_t)h * max_pages, p_begin, p_cand_end, ppw,
                     q_obs, NS, Hq, Hkv, W, s, kv, qb, active, qf);
   const int32_t* s_table = reinterpret_cast<const int32_t*>(smem + L::TABLE);
   const uint32_t* s_mask = reinterpret_cast<const uint32_t*>(smem + L::MASK);
@@ -1273,7 +1314,7 @@ void score_rows_kernel(
     const T* __restrict__ q_obs, const T* __restrict__ k_pool, const int32_t* __restrict__ table,
     const uint16_t* __restrict__ masks, const int32_t* __restrict__ n_pages_arr, int NS, int Hq,
     int Hkv, int W, int max_pages, int L_dense, float c2, const float* __restrict__ row_lse,
-    float* __restrict__ a_rows) {
+    float* __restrict__ a_rows, int ppw) {
   using F = Frag<T, D>;
   constexpr int R_pad = 32 * QB;
   extern __shared__ __align__(16) char smem[];
@@ -1286,7 +1327,7 @@ void score_rows_kernel(
   const int cand_len = HK_PAGE * max(0, n - dense_pages(L_dense));
   const int32_t* trow = table + (size_t)h * max_pages;
   const uint16_t* mrow = masks + (size_t)h * max_pages;
-  const int p_begin = chunk * SCORE_PPW, p_end_all = min(p_begin + SCORE_PPW, max_pages);
+  const int p_begin = chunk * ppw, p_end_all = min(p_begin + ppw, max_pages);
   const int p_cand_end = min(p_end_all, cand_len / HK_PAGE);
   float* arow = a_rows + (size_t)h * R * S_max;
 
@@ -1357,14 +1398,14 @@ hipError_t launch_score_rows_q(int NS, int Hq, int Hkv, int W, const void* q_obs
                                const float* row_lse, float* a_rows, hipStream_t st) {
   constexpr int R_pad = 32 * QB;
   const int n_heads = NS * Hkv;
-  const int n_chunks = (kv->max_pages + SCORE_PPW - 1) / SCORE_PPW;
+  const int ppw = score_ppw_t<T>(n_heads, kv->max_pages), n_chunks = (kv->max_pages + ppw - 1) / ppw;
   const size_t lds = (size_t)R_pad * D * sizeof(T) + (size_t)R_pad * sizeof(float);
   allow_dynamic_lds<score_rows_kernel<T, D, QB>>(lds);
   TimedLaunch t(HK_TK_SCORE_ROWS, st);
   hipLaunchKernelGGL((score_rows_kernel<T, D, QB>), dim3(n_chunks, n_heads), dim3(SCORE_NT), lds, st,
                      static_cast<const T*>(q_obs), static_cast<const T*>(kv->k_pool), kv->page_table,
                      kv->page_mask, kv->n_pages, NS, Hq, Hkv, W, kv->max_pages, L_dense,
-                     sm_scale * kLog2e, row_lse, a_rows);
+                     sm_scale * kLog2e, row_lse, a_rows, ppw);
   return hipGetLastError();
 }
 
@@ -1381,12 +1422,24 @@ hipError_t launch_score_rows_t(int NS, int Hq, int Hkv, int W, const void* q_obs
   }
 }
 
+// Workspace bytes for this many chunks per head: the chunks' (max, sum) of every row, then
+// the row LSEs (when the caller takes none).
+static size_t score_ws(long long n_heads, long long n_chunks, int R_pad, long long n_lse) {
+  const size_t part = ((size_t)(n_heads * n_chunks) * R_pad * sizeof(float2) + 255) & ~(size_t)255;
+  return part + (((size_t)n_lse * sizeof(float) + 255) & ~(size_t)255);
+}
+
 template <typename T, int D, int QB>
 hipError_t launch_score_q(const hk_score_args& a, hipStream_t st) {
   const hk_paged_kv* kv = a.kv;
   constexpr int R_pad = 32 * QB;
   const int n_heads = a.NS * a.Hkv;
-  const int n_chunks = (kv->max_pages + SCORE_PPW - 1) / SCORE_PPW;
+  // pass 1 leaves one partial per (head, chunk, row) in the workspace: a workspace that only
+  // holds those of SCORE_PPW-page chunks gets such chunks
+  const int ppw2 = score_ppw_t<T>(n_heads, kv->max_pages);
+  const int ppw = a.row_lse_in || a.ws_bytes >= score_ws(n_heads, (kv->max_pages + ppw2 - 1) / ppw2, R_pad, a.W * a.NS * a.Hq)
+                      ? ppw2 : SCORE_PPW;
+  const int n_chunks = (kv->max_pages + ppw - 1) / ppw;
   const float c2 = a.sm_scale * kLog2e;
   char* ws = static_cast<char*>(a.ws);
   float2* part = reinterpret_cast<float2*>(ws);
@@ -1394,26 +1447,25 @@ hipError_t launch_score_q(const hk_score_args& a, hipStream_t st) {
   const size_t off = ((size_t)n_heads * n_chunks * R_pad * sizeof(float2) + 255) & ~(size_t)255;
   if (!lse_buf) lse_buf = reinterpret_cast<float*>(ws + off);
   const float* lse_use = a.row_lse_in;
-  dim3 grid(n_chunks, n_heads);
+  const dim3 grid(n_chunks, n_heads), grid2((kv->max_pages + ppw2 - 1) / ppw2, n_heads);
   // bf16 caches: the cooperative passes; fp32 caches (and the redundancy variant of pass 2):
   // the per-wave tile passes
   constexpr bool coop = sizeof(T) == 2;
   if (!lse_use) {
     if constexpr (coop) {
       using Cp = Coop<D, QB>;
-      const int nc = (kv->max_pages + Cp::PPW - 1) / Cp::PPW;      // <= n_chunks (workspace size)
       const size_t lds = CoopLds<D, QB>::TOTAL;
       allow_dynamic_lds<score_pass1_coop_kernel<D, QB>>(lds);
       {
         TimedLaunch t(HK_TK_SCORE_PASS1, st);
-        hipLaunchKernelGGL((score_pass1_coop_kernel<D, QB>), dim3(nc, n_heads), dim3(Cp::NT), lds, st,
+        hipLaunchKernelGGL((score_pass1_coop_kernel<D, QB>), grid, dim3(Cp::NT), lds, st,
                            static_cast<const uint16_t*>(a.q_obs), static_cast<const uint16_t*>(kv->k_pool),
                            kv->page_table, kv->page_mask, kv->n_pages, a.NS, a.Hq, a.Hkv, a.W,
-                           kv->max_pages, c2, part, nc);
+                           kv->max_pages, c2, part, n_chunks, ppw);
       }
       {
         TimedLaunch t(HK_TK_SCORE_MERGE, st);
-        hipLaunchKernelGGL(score_lse_merge_kernel, dim3(n_heads), dim3(256), 0, st, part, nc,
+        hipLaunchKernelGGL(score_lse_merge_kernel, dim3(n_heads), dim3(256), 0, st, part, n_chunks,
                            R_pad, a.NS, a.Hq, a.Hkv, a.W, c2, a.sm_scale, lse_buf, kv->n_pages,
                            a.L_dense, a.cand_len);
       }
@@ -1427,7 +1479,7 @@ hipError_t launch_score_q(const hk_score_args& a, hipStream_t st) {
         hipLaunchKernelGGL((score_pass1_kernel<T, D, QB>), grid, dim3(SCORE_NT), lds1, st,
                            static_cast<const T*>(a.q_obs), static_cast<const T*>(kv->k_pool),
                            kv->page_table, kv->page_mask, kv->n_pages, a.NS, a.Hq, a.Hkv, a.W,
-                           kv->max_pages, c2, part, n_chunks);
+                           kv->max_pages, c2, part, n_chunks, ppw);
       }
       {
         TimedLaunch t(HK_TK_SCORE_MERGE, st);
@@ -1446,30 +1498,29 @@ hipError_t launch_score_q(const hk_score_args& a, hipStream_t st) {
   const size_t lds2 = pass2_lds(R_pad, D, sizeof(T), a.x_red != nullptr);
   TimedLaunch t(HK_TK_SCORE_PASS2, st);
   if (a.x_red) {
-    constexpr int PPW2 = P2Shape<true>::PPW;
-    const dim3 grid2((kv->max_pages + PPW2 - 1) / PPW2, n_heads);
+    const int ppwr = score_ppw_rounds(n_heads, kv->max_pages, P2Shape<true>::PPW, 2 * SCORE_PPW_MIN, 48);
+    const dim3 gridr((kv->max_pages + ppwr - 1) / ppwr, n_heads);
     allow_dynamic_lds<score_pass2_kernel<T, D, QB, true>>(lds2);
-    hipLaunchKernelGGL((score_pass2_kernel<T, D, QB, true>), grid2, dim3(P2Shape<true>::NT), lds2, st,
+    hipLaunchKernelGGL((score_pass2_kernel<T, D, QB, true>), gridr, dim3(P2Shape<true>::NT), lds2, st,
                        static_cast<const T*>(a.q_obs), static_cast<const T*>(kv->k_pool),
                        kv->page_table, kv->page_mask, kv->n_pages, a.NS, a.Hq, a.Hkv, a.W,
                        kv->max_pages, a.L_dense, c2, lnR, lse_use, a.s_attn, a.cand_len,
-                       a.ref_slots, a.n_ref, a.x_red);
+                       a.ref_slots, a.n_ref, a.x_red, ppwr);
   } else if constexpr (coop) {
     using Cp = Coop<D, QB>;
     const size_t lds = CoopLds<D, QB>::TOTAL;
     allow_dynamic_lds<score_pass2_coop_kernel<D, QB>>(lds);
-    hipLaunchKernelGGL((score_pass2_coop_kernel<D, QB>), dim3((kv->max_pages + Cp::PPW - 1) / Cp::PPW, n_heads),
-                       dim3(Cp::NT), lds, st, static_cast<const uint16_t*>(a.q_obs),
+    hipLaunchKernelGGL((score_pass2_coop_kernel<D, QB>), grid2, dim3(Cp::NT), lds, st, static_cast<const uint16_t*>(a.q_obs),
                        static_cast<const uint16_t*>(kv->k_pool), kv->page_table, kv->page_mask,
                        kv->n_pages, a.NS, a.Hq, a.Hkv, a.W, kv->max_pages, a.L_dense, c2, lnR, lse_use,
-                       a.s_attn, a.cand_len);
+                       a.s_attn, a.cand_len, ppw2);
   } else {
     allow_dynamic_lds<score_pass2_kernel<T, D, QB, false>>(lds2);
-    hipLaunchKernelGGL((score_pass2_kernel<T, D, QB, false>), grid, dim3(P2Shape<false>::NT), lds2, st,
+    hipLaunchKernelGGL((score_pass2_kernel<T, D, QB, false>), grid2, dim3(P2Shape<false>::NT), lds2, st,
                        static_cast<const T*>(a.q_obs), static_cast<const T*>(kv->k_pool),
                        kv->page_table, kv->page_mask, kv->n_pages, a.NS, a.Hq, a.Hkv, a.W,
                        kv->max_pages, a.L_dense, c2, lnR, lse_use, a.s_attn, a.cand_len,
-                       nullptr, 0, nullptr);
+                       nullptr, 0, nullptr, ppw2);
   }
   return hipGetLastError();
 }
@@ -1487,13 +1538,19 @@ hipError_t launch_score_t(const hk_score_args& a, hipStream_t st) {
 
 }  // namespace hk
 
-size_t hk_score_ws(int NS, int Hq, int Hkv, int D, int W, int max_pages) {
-  (void)D;
-  const int R_pad = hk::score_rpad(Hq / Hkv * W);
-  const int n_chunks = (max_pages + hk::SCORE_PPW - 1) / hk::SCORE_PPW;
-  const size_t part = ((size_t)NS * Hkv * n_chunks * R_pad * sizeof(float2) + 255) & ~(size_t)255;
-  const size_t lse = ((size_t)W * NS * Hq * sizeof(float) + 255) & ~(size_t)255;
-  return part + lse;
+size_t hk_score_ws_min(int NS, int Hq, int Hkv, int W, int max_pages) {
+  return hk::score_ws(NS * Hkv, (max_pages + hk::SCORE_PPW - 1) / hk::SCORE_PPW,
+                      hk::score_rpad(Hq / Hkv * W), W * NS * Hq);
+}
+
+// Few heads take shorter chunks, so more partials than hk_score_ws_min counts: at most
+// SCORE_MAX_PARTS in all, of at least SCORE_PPW_MIN pages each.  Counting that bound instead
+// of the chunks of this very size keeps the bytes monotone in the heads and in the table width.
+size_t hk_score_ws(int NS, int Hq, int Hkv, int W, int max_pages) {
+  const long long H = (long long)NS * Hkv, most = H * ((max_pages + hk::SCORE_PPW_MIN - 1) / hk::SCORE_PPW_MIN);
+  const long long parts = std::max(H * ((max_pages + hk::SCORE_PPW - 1) / hk::SCORE_PPW),
+                                   std::min(most, (long long)hk::SCORE_MAX_PARTS));
+  return hk::score_ws(parts, 1, hk::score_rpad(Hq / Hkv * W), (long long)W * NS * Hq);
 }
 
 size_t hk_score_lds_bytes(int R, int D, int esize, bool redundancy) {

@@ -2,12 +2,13 @@
 (splits per row, rows per workgroup, chunk lengths), against the CPU oracle."""
 import math
 
+import numpy as np
 import pytest
 import torch
 
 import oracle as O
 import workload as WL
-from hk_testlib import RTOL, HostCache, check_lse, check_prob, np64
+from hk_testlib import RTOL, HostCache, check_lse, check_log_scores, check_prob, np64, q_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -50,3 +51,48 @@ def _decode_against_oracle(cfg, lens, max_pages, hole_prob=0.1, n_split=None, q_
 def test_decode_merge_shapes(D, G, dtype, pages):
     cfg = dict(L=1, B=3, Hq=G, Hkv=1, D=D, N=pages * 16, dtype=dtype, W=8, seed=41, recipe="normal")
     _decode_against_oracle(cfg, [pages * 16, 0, pages * 8 + 5], pages, n_split=-(-pages // 16))
+
+
+# chunks of 16 pages up to 128: few rows take short ones; rows that end before, at and past a
+# chunk's edge, or hold nothing.  The least workspace the call accepts holds the partials of
+# 128-page chunks only and gets those.
+@pytest.mark.parametrize("D,G,dtype,pages,lens", [
+    (64, 4, "f32", 130, [2080, 256, 257, 0]), (128, 4, "bf16", 130, [2080, 255, 16, 1]),
+    (128, 7, "bf16", 40, [640, 512, 513, 300]), (64, 8, "bf16", 66, [1056, 1, 1024, 1025])])
+@pytest.mark.parametrize("least", [False, True])
+def test_score_chunk_lengths(D, G, dtype, pages, lens, least):
+    import paper_2606_28831_amd as hk
+    W, NS, Hkv = 16, 2, 2
+    cfg = dict(L=1, B=NS, Hq=Hkv * G, Hkv=Hkv, D=D, N=pages * 16, dtype=dtype, W=W, seed=43, recipe="normal")
+    w = WL.make_workload(cfg, DEV, hole_prob=0.1, head_lens=lens, max_pages=pages)
+    kv = hk.PagedKV(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
+    d = hk.dims(NS, Hkv * G, Hkv, D, W)
+    H, R = NS * Hkv, G * W
+    blocks = next(b for b in (1, 2, 4, 7, 8) if 32 * b >= R)
+    small = -(-H * -(-pages // 128) * 32 * blocks * 8 // 256) * 256 + -(-W * NS * Hkv * G * 4 // 256) * 256
+    ws = hk.workspace(hk.OP_SCORE, d, w.max_pages, DEV)
+    assert ws.numel() > small
+    if least:
+        ws = ws[:small]
+    ws.fill_(255)
+    s = torch.full((H, w.S_max), 7.0, device=DEV)
+    cl = torch.empty(H, dtype=torch.int32, device=DEV)
+    lse = torch.empty(W, NS, Hkv * G, device=DEV)
+    scale = 1 / math.sqrt(D)
+    hk.hk_score(d, w.q_obs, kv, 48, scale, s, cl, row_lse_out=lse, ws=ws)
+    if least:
+        with pytest.raises(hk.HardKVError):
+            hk.hk_score(d, w.q_obs, kv, 48, scale, s, cl, row_lse_out=lse, ws=ws[:small - 256])
+    torch.cuda.synchronize()
+    host = HostCache(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
+    qn, sn, ln, rtol = np64(w.q_obs), np64(s), np64(lse), RTOL[dtype]
+    for h in range(H):
+        sq, kvh = divmod(h, Hkv)
+        K, valid = host.head(h)
+        n_cand = 16 * max(0, int(w.n_pages[h]) - 3)
+        assert int(cl[h]) == n_cand
+        ref_s, ref_l = O.score_head(q_rows(qn, h, Hkv, G), K, valid, n_cand, scale)
+        full = np.full(w.S_max, -np.inf)
+        full[:len(ref_s)] = ref_s
+        check_log_scores(sn[h], full, rtol, f"s head {h}")
+        check_lse(ln[:, sq, kvh * G:(kvh + 1) * G].reshape(-1), ref_l, rtol, f"lse head {h}")
