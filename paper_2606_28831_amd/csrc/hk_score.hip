@@ -1545,11 +1545,12 @@ size_t hk_score_ws_min(int NS, int Hq, int Hkv, int W, int max_pages) {
 
 // Few heads take shorter chunks, so more partials than hk_score_ws_min counts: at most
 // SCORE_MAX_PARTS in all, of at least SCORE_PPW_MIN pages each.  Counting that bound instead
-// of the chunks of this very size keeps the bytes monotone in the heads and in the table width.
+// of the chunks of this very size, on top of the SCORE_PPW-page ones, keeps the bytes
+// growing with the heads and with the table width.
 size_t hk_score_ws(int NS, int Hq, int Hkv, int W, int max_pages) {
   const long long H = (long long)NS * Hkv, most = H * ((max_pages + hk::SCORE_PPW_MIN - 1) / hk::SCORE_PPW_MIN);
-  const long long parts = std::max(H * ((max_pages + hk::SCORE_PPW - 1) / hk::SCORE_PPW),
-                                   std::min(most, (long long)hk::SCORE_MAX_PARTS));
+  const long long parts = H * ((max_pages + hk::SCORE_PPW - 1) / hk::SCORE_PPW) +
+                          std::min(most, (long long)hk::SCORE_MAX_PARTS);
   return hk::score_ws(parts, 1, hk::score_rpad(Hq / Hkv * W), (long long)W * NS * Hq);
 }
 
