@@ -27,6 +27,8 @@
 // target = ceil(p_q * Total / 10^6), the smallest set in (key desc, slot desc) order whose
 // weight reaches the target, then the count clamp; every quantity is an exact integer, so
 // the result does not depend on how the work is split.
+#include <algorithm>
+
 #include "hk_internal.h"
 
 namespace hk {
@@ -44,15 +46,18 @@ constexpr int SW_B3 = 1024;                    // level 3: bits 9..0
 constexpr uint32_t SW_LOW = (1u << SW_SH1) - 1u;
 constexpr int SW_TSH = 7;                      // ties counted per block of 128 slots
 constexpr int SW_LIST = 32768;                 // keys of one digit the finishing workgroup holds
+constexpr int SW_SHORT = 12288;                // row slots up to which two finish workgroups fit a CU
+constexpr int SW_LIST_MIN = SW_B1 * 4;         // the level-1 half sums use the list's space
 constexpr int SW_CMAX = 128;                   // chunks per head at most (S_max <= 262144)
 constexpr uint32_t SW_NONE = 0xffffffffu;      // key of a non-candidate / no threshold
 // a packed histogram entry: count << 52 | weight (a chunk's count <= 2048 < 2^12 and its
 // weight <= 2048 * 2^40 < 2^52, so neither field overflows into the other)
 constexpr int SW_CNT_SH = 52;
 constexpr unsigned long long SW_WMASK = (1ull << SW_CNT_SH) - 1ull;
-constexpr size_t SW_LDS = (size_t)SW_LIST * 4 + SW_B2 * 12;   // dynamic LDS of finish
 static_assert(SW_B1 == 2 * SW_NT && SW_B1 * 2 == SW_FT && SW_B2 == 2 * SW_FT && SW_B3 == SW_FT,
               "bins per thread");
+constexpr int SW_FS = 512;                     // threads of the finishing workgroup of short rows
+static_assert(SW_B1 == SW_FS && SW_SHORT <= 32 * SW_FS, "one digit, one bitmap word per thread");
 static_assert(SW_CH == 2 * 4 * SW_NT, "two float4 per thread and chunk");
 
 // Fixed-point weight floor(v * 2^40) of a value v in [0, 1] from its bits, as its two exact
@@ -96,6 +101,20 @@ __device__ __forceinline__ unsigned long long sw_uniform(unsigned long long x) {
   return ((unsigned long long)hi << 32) | lo;
 }
 
+// Chunks of a head to be worked on: those that can hold a candidate when `skip`, else all.
+// The others (a table wider than the row, or the dense tier) write no pieces, histogram or
+// keys, and nothing reads theirs: prep, chunk and bitmap leave them at once (but for the
+// zeros of c_out and of the bitmap), and pieces and histograms are summed over the live
+// chunks.  1024 heads of 1200 to 3100 tokens in a 12288-slot table: prep 13.8 -> 8.6 us,
+// chunk 23 -> 16, bitmap 13.8 -> 6.6.  A launch whose workgroups all run at once does not
+// skip: knowing the head's candidates first delays its loads by a memory round trip (8 heads
+// x 8192 slots: 51.2 us for score and selection, 52.4 with skipping).
+constexpr int SW_RESIDENT = 2048;              // 256-thread workgroups the chip holds at once
+__device__ __forceinline__ int sw_live(int h, int C, int S_max, const int32_t* __restrict__ cand_len,
+                                       int skip) {
+  return skip ? min(C, (min(cand_len[h], S_max) + SW_CH - 1) / SW_CH) : C;
+}
+
 // The thread's four consecutive slots of half r of chunk c start at this slot.
 __device__ __forceinline__ int sw_group(int c, int r) {
   return c * SW_CH + r * (SW_CH / 2) + (int)threadIdx.x * 4;
@@ -135,12 +154,13 @@ __device__ __forceinline__ void sw_load8(const float* __restrict__ row, int c, i
 }
 
 __global__ __launch_bounds__(SW_NT) void sw_prep_kernel(
-    int S_max, int C, const int32_t* __restrict__ cand_len, const uint16_t* __restrict__ mask,
-    int n_metrics, const float* __restrict__ x0, const float* __restrict__ x1,
+    int S_max, int C, int skip, const int32_t* __restrict__ cand_len,
+    const uint16_t* __restrict__ mask, int n_metrics, const float* __restrict__ x0, const float* __restrict__ x1,
     const float* __restrict__ T0, const float* __restrict__ T1, float2* __restrict__ part) {
   __shared__ float red[2][SW_NW];
   const int c = (int)blockIdx.x % C, h = (int)blockIdx.x / C, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
+  if (c >= sw_live(h, C, S_max, cand_len, skip)) return;
   const uint32_t cb = sw_cand(h, c, S_max, cand_len, mask);
   for (int m = 0; m < n_metrics; ++m) {
     const float* Tp = (m == 0 ? T0 : T1);
@@ -173,8 +193,8 @@ __global__ __launch_bounds__(SW_NT) void sw_prep_kernel(
 
 template <bool CALIB>
 __global__ __launch_bounds__(SW_NT) void sw_chunk_kernel(
-    int S_max, int C, const int32_t* __restrict__ cand_len, const uint16_t* __restrict__ mask,
-    int n_metrics, const float* __restrict__ x0, const float* __restrict__ x1,
+    int S_max, int C, int skip, const int32_t* __restrict__ cand_len,
+    const uint16_t* __restrict__ mask, int n_metrics, const float* __restrict__ x0, const float* __restrict__ x1,
     const float* __restrict__ T0, const float* __restrict__ T1, float w0, float w1,
     const float2* __restrict__ part, const float* __restrict__ c_in, float* __restrict__ c_out,
     float* __restrict__ lse_out, unsigned long long* __restrict__ hp, uint16_t* __restrict__ ho,
@@ -186,6 +206,17 @@ __global__ __launch_bounds__(SW_NT) void sw_chunk_kernel(
   __shared__ float s_lse[2];
   const int c = (int)blockIdx.x % C, h = (int)blockIdx.x / C, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
+  const int live = sw_live(h, C, S_max, cand_len, skip);
+  if (c >= live) {
+    if (CALIB && c_out)
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+        if (sw_group(c, r) < S_max)
+          *reinterpret_cast<float4*>(c_out + (size_t)h * S_max + sw_group(c, r)) = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (CALIB && lse_out && live <= 0 && c == 0 && tid < n_metrics)
+      lse_out[(size_t)h * n_metrics + tid] = -INFINITY;      // a head without candidates
+    return;
+  }
   const uint32_t cb = sw_cand(h, c, S_max, cand_len, mask);
   hist[tid] = 0ull;
   hist[tid + SW_NT] = 0ull;
@@ -197,10 +228,10 @@ __global__ __launch_bounds__(SW_NT) void sw_chunk_kernel(
     for (int m = 0; m < 2; ++m)
       if (m < n_metrics) sw_load8((m == 0 ? x0 : x1) + (size_t)h * S_max, c, S_max, t[m]);
     if (wave < n_metrics) {
-      // the head's log-sum-exp of metric `wave` from its C chunk pieces (lanes q, q + 64)
+      // the head's log-sum-exp of metric `wave` from its chunk pieces (lanes q, q + 64)
       const float2* pp = part + (size_t)h * C * 2 + wave;
-      const float2 a = lane < C ? pp[lane * 2] : make_float2(-INFINITY, 0.f);
-      const float2 b = lane + 64 < C ? pp[(lane + 64) * 2] : make_float2(-INFINITY, 0.f);
+      const float2 a = lane < live ? pp[lane * 2] : make_float2(-INFINITY, 0.f);
+      const float2 b = lane + 64 < live ? pp[(lane + 64) * 2] : make_float2(-INFINITY, 0.f);
       const float M = wave_max(fmaxf(a.x, b.x));
       float L = 0.f;
       if (M != -INFINITY) {
@@ -332,7 +363,7 @@ struct SwPick {
 // target's 64-bit arithmetic runs on the scalar unit.  aw0 / ac0 are the weight and count above this level's bins.  The target is
 // target_of(total weight, total count) of the level (returned in *target, with the totals);
 // for a target of 0 no digit is picked.  Two barriers; the results come back through LDS.
-template <int BPT, int NB, typename TF>
+template <int FT, int BPT, int NB, typename TF>
 __device__ __forceinline__ SwPick sw_pick(const unsigned long long (&bw)[BPT],
                                           const unsigned long long (&bc)[BPT], bool by_count,
                                           TF target_of, unsigned long long aw0,
@@ -354,7 +385,7 @@ __device__ __forceinline__ SwPick sw_pick(const unsigned long long (&bw)[BPT],
   __syncthreads();
   unsigned long long pw = 0, pc = 0, tw = 0, tc = 0;
 #pragma unroll
-  for (int w = 0; w < SW_FW; ++w) {
+  for (int w = 0; w < FT / 64; ++w) {
     const unsigned long long a = sh.rw[w], n = sh.rc[w];
     if (w < wave) {
       pw += a;
@@ -420,18 +451,18 @@ struct SwFound {
 // chunk), from the LDS list or from the chunks' segments.  With BY_CHUNK (or from the
 // segments) one wave walks one chunk's elements at a time, which gives q; otherwise the
 // list is walked flat and q is -1.
-template <bool BY_CHUNK, typename F>
+template <int FT, bool BY_CHUNK, typename F>
 __device__ __forceinline__ void sw_for_each(const SwFound& r, const uint32_t* list, const SwSh& sh,
                                             F f) {
   if (r.list_mode && !BY_CHUNK) {
-    for (uint32_t i = threadIdx.x; i < r.seg.n; i += SW_FT) {
+    for (uint32_t i = threadIdx.x; i < r.seg.n; i += FT) {
       const uint32_t p = list[i];
       f(r.seg.key_of(p), i, p, -1);
     }
     return;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int q = wave; q < r.seg.C; q += SW_FW) {
+  for (int q = wave; q < r.seg.C; q += FT / 64) {
     const uint32_t pre = sh.seg_pre[q];
     const uint32_t n = (q + 1 < r.seg.C ? sh.seg_pre[q + 1] : r.seg.n) - pre;
     const uint32_t* src = r.list_mode ? list + pre : r.seg.srow + (size_t)q * SW_CH + sh.seg_off[q];
@@ -453,21 +484,21 @@ __device__ __forceinline__ void sw_for_each(const SwFound& r, const uint32_t* li
 
 // One lower level: the histogram of the NB = 2^bits key values at `shift` over the elements
 // whose bits above them equal `prefix`, then the pick against the fixed target.
-template <int NB>
+template <int FT, int NB>
 __device__ __forceinline__ SwPick sw_level(const SwFound& r, const uint32_t* list, uint32_t prefix,
                                            int shift,
                                            bool by_count, unsigned long long target,
                                            const SwPick& above, unsigned long long* hw2,
                                            uint32_t* hc2, SwSh& sh) {
-  constexpr int BPT = NB / SW_FT, BITS = NB == 2048 ? 11 : 10;
+  constexpr int BPT = NB / FT, BITS = NB == 2048 ? 11 : 10;
   const int tid = threadIdx.x;
 #pragma unroll
   for (int b = 0; b < BPT; ++b) {
-    hw2[b * SW_FT + tid] = 0ull;
-    hc2[b * SW_FT + tid] = 0u;
+    hw2[b * FT + tid] = 0ull;
+    hc2[b * FT + tid] = 0u;
   }
   __syncthreads();
-  sw_for_each<false>(r, list, sh, [&](uint32_t k, uint32_t, uint32_t, int) {
+  sw_for_each<FT, false>(r, list, sh, [&](uint32_t k, uint32_t, uint32_t, int) {
     if ((k >> (shift + BITS)) == prefix) {
       const uint32_t b = (k >> shift) & (NB - 1);
       atomicAdd(&hw2[b], sw_weight(k));
@@ -482,14 +513,14 @@ __device__ __forceinline__ SwPick sw_level(const SwFound& r, const uint32_t* lis
     bc[b] = hc2[NB - 1 - (BPT * tid + b)];
   }
   unsigned long long tg, tw, tc;
-  return sw_pick<BPT, NB>(bw, bc, by_count, SwFixed{target}, above.aw, above.ac, &tg, &tw, &tc, sh);
+  return sw_pick<FT, BPT, NB>(bw, bc, by_count, SwFixed{target}, above.aw, above.ac, &tg, &tw, &tc, sh);
 }
 
 // The largest key v whose criterion summed over keys >= v reaches the target (weights, or
 // counts when by_count), target = target_of(total weight, total count) -- returned in
 // *target with the totals -- from the head's level-1 histogram (bw1 / bc1: this thread's
 // digit) and the chunks' sorted segments of the picked digit.
-template <typename TF>
+template <int FT, typename TF>
 __device__ __forceinline__ SwFound sw_search(const unsigned long long (&bw1)[1],
                                              const unsigned long long (&bc1)[1], bool by_count,
                                              TF target_of, unsigned long long* target,
@@ -497,7 +528,7 @@ __device__ __forceinline__ SwFound sw_search(const unsigned long long (&bw1)[1],
                                              const unsigned long long* __restrict__ hprow,
                                              const uint16_t* __restrict__ horow,
                                              const uint32_t* __restrict__ srow, int C,
-                                             uint32_t* list, unsigned long long* hw2,
+                                             uint32_t list_cap, uint32_t* list, unsigned long long* hw2,
                                              uint32_t* hc2, SwSh& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   SwFound r;
@@ -506,7 +537,7 @@ __device__ __forceinline__ SwFound sw_search(const unsigned long long (&bw1)[1],
   r.aw = r.ac = r.ntie = 0;
   r.list_mode = false;
   r.seg = SwSeg{srow, 0u, 0u, C};
-  const SwPick p1 = sw_pick<1, SW_B1>(bw1, bc1, by_count, target_of, 0ull, 0ull, target, tot_w,
+  const SwPick p1 = sw_pick<FT, 1, SW_B1>(bw1, bc1, by_count, target_of, 0ull, 0ull, target, tot_w,
                                       tot_c, sh);
   const unsigned long long tg = *target;
   if (tg == 0) return r;
@@ -526,17 +557,17 @@ __device__ __forceinline__ SwFound sw_search(const unsigned long long (&bw1)[1],
   if (wave == 1) sh.seg_pre[64 + lane] += sh.seg_tot0;
   __syncthreads();
   r.seg = SwSeg{srow, d1, (uint32_t)p1.c, C};
-  r.list_mode = p1.c <= SW_LIST;
+  r.list_mode = p1.c <= list_cap;
   if (r.list_mode) {
     // one wave per chunk: its segment, contiguous, into the list at the segment's prefix
     r.list_mode = false;
-    sw_for_each<true>(r, list, sh, [&](uint32_t, uint32_t i, uint32_t p, int) { list[i] = p; });
+    sw_for_each<FT, true>(r, list, sh, [&](uint32_t, uint32_t i, uint32_t p, int) { list[i] = p; });
     r.list_mode = true;
     __syncthreads();
   }
-  const SwPick p2 = sw_level<SW_B2>(r, list, d1, SW_SH2, by_count, tg, p1, hw2, hc2, sh);
+  const SwPick p2 = sw_level<FT, SW_B2>(r, list, d1, SW_SH2, by_count, tg, p1, hw2, hc2, sh);
   const uint32_t pre = (d1 << 11) | p2.d;
-  const SwPick p3 = sw_level<SW_B3>(r, list, pre, 0, by_count, tg, p2, hw2, hc2, sh);
+  const SwPick p3 = sw_level<FT, SW_B3>(r, list, pre, 0, by_count, tg, p2, hw2, hc2, sh);
   r.v = (pre << 10) | p3.d;
   r.aw = p3.aw;
   r.ac = p3.ac;
@@ -544,52 +575,61 @@ __device__ __forceinline__ SwFound sw_search(const unsigned long long (&bw1)[1],
   return r;
 }
 
-__global__ __launch_bounds__(SW_FT) void sw_finish_kernel(
-    int S_max, int C, const unsigned long long* __restrict__ hp, const uint16_t* __restrict__ ho,
+// FT threads: SW_FT, or SW_FS for rows of up to SW_SHORT slots in a launch of more heads than
+// CUs, whose list leaves LDS for a second workgroup on the CU (1024 heads in a 12288-slot
+// table: 41 us with one 1024-thread workgroup per CU).
+template <int FT>
+__global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(4, 8))) void sw_finish_kernel(
+    int S_max, int C_all, int skip, const int32_t* __restrict__ cand_len, int list_cap,
+    const unsigned long long* __restrict__ hp, const uint16_t* __restrict__ ho,
     const uint32_t* __restrict__ sorted, int p_q, int k_min, int k_max, uint4* __restrict__ params,
     int32_t* __restrict__ k_out, float* __restrict__ sel_mass) {
   extern __shared__ __align__(16) unsigned char sw_dyn[];
   __shared__ SwSh sh;
   const int h = blockIdx.x, tid = threadIdx.x;
   uint32_t* list = reinterpret_cast<uint32_t*>(sw_dyn);
-  unsigned long long* hw2 = reinterpret_cast<unsigned long long*>(sw_dyn + (size_t)SW_LIST * 4);
-  uint32_t* hc2 = reinterpret_cast<uint32_t*>(sw_dyn + (size_t)SW_LIST * 4 + SW_B2 * 8);
+  unsigned long long* hw2 = reinterpret_cast<unsigned long long*>(sw_dyn + (size_t)list_cap * 4);
+  uint32_t* hc2 = reinterpret_cast<uint32_t*>(sw_dyn + (size_t)list_cap * 4 + SW_B2 * 8);
+  const int C = sw_live(h, C_all, S_max, cand_len, skip);
   // the halves of the level-1 sums, in the list's space before the list is used
   unsigned long long(*s_half)[SW_B1] = reinterpret_cast<unsigned long long(*)[SW_B1]>(sw_dyn);
-  const unsigned long long* hprow = hp + (size_t)h * C * SW_B1;
-  const uint16_t* horow = ho + (size_t)h * C * SW_B1;
+  const unsigned long long* hprow = hp + (size_t)h * C_all * SW_B1;
+  const uint16_t* horow = ho + (size_t)h * C_all * SW_B1;
   const uint32_t* srow = sorted + (size_t)h * S_max;
 
-  // the head's level-1 histogram: threads t and t + 512 sum digit 511 - t over the even and
-  // the odd chunks; thread t < 512 then holds the digit's total
+  // the head's level-1 histogram: thread t < 512 holds the total of digit 511 - t; with 1024
+  // threads, threads t and t + 512 first sum it over the even and the odd chunks
   unsigned long long bw1[1] = {0ull}, bc1[1] = {0ull};
   {
-    const int d = SW_B1 - 1 - (tid & (SW_B1 - 1)), half = tid >> 9;
+    constexpr int HV = FT / SW_B1, U = FT == SW_FT ? 16 : SW_SHORT / SW_CH;
+    const int d = SW_B1 - 1 - (tid & (SW_B1 - 1)), half = tid / SW_B1;
     const unsigned long long* pp = hprow + d;
-    for (int q0 = half; q0 < C; q0 += 32) {
-      unsigned long long a[16];
+    for (int q0 = half; q0 < C; q0 += HV * U) {
+      unsigned long long a[U];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int q = q0 + 2 * u;
+      for (int u = 0; u < U; ++u) {
+        const int q = q0 + HV * u;
         a[u] = q < C ? pp[(size_t)q * SW_B1] : 0ull;
       }
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
+      for (int u = 0; u < U; ++u) {
         bw1[0] += a[u] & SW_WMASK;
         bc1[0] += a[u] >> SW_CNT_SH;
       }
     }
-    if (half) {
-      s_half[0][tid - SW_B1] = bw1[0];
-      s_half[1][tid - SW_B1] = bc1[0];
-    }
-    __syncthreads();
-    if (half) {
-      bw1[0] = 0ull;
-      bc1[0] = 0ull;
-    } else {
-      bw1[0] += s_half[0][tid];
-      bc1[0] += s_half[1][tid];
+    if constexpr (HV == 2) {
+      if (half) {
+        s_half[0][tid - SW_B1] = bw1[0];
+        s_half[1][tid - SW_B1] = bc1[0];
+      }
+      __syncthreads();
+      if (half) {
+        bw1[0] = 0ull;
+        bc1[0] = 0ull;
+      } else {
+        bw1[0] += s_half[0][tid];
+        bc1[0] += s_half[1][tid];
+      }
     }
   }
 
@@ -599,8 +639,8 @@ __global__ __launch_bounds__(SW_FT) void sw_finish_kernel(
     return pq * (tw / 1000000ull) + (pq * (tw % 1000000ull) + 999999ull) / 1000000ull;
   };
   unsigned long long target, tot_w, tot_c;
-  SwFound f = sw_search(bw1, bc1, false, mass_target, &target, &tot_w, &tot_c, hprow, horow,
-                        srow, C, list, hw2, hc2, sh);
+  SwFound f = sw_search<FT>(bw1, bc1, false, mass_target, &target, &tot_w, &tot_c, hprow, horow,
+                        srow, C, (uint32_t)list_cap, list, hw2, hc2, sh);
   const int n_cand = (int)tot_c;
   unsigned long long take = 0, wv = 0;
   long long k = 0;
@@ -623,8 +663,8 @@ __global__ __launch_bounds__(SW_FT) void sw_finish_kernel(
       wv = 0;
     } else {
       unsigned long long t2, w2, c2;
-      f = sw_search(bw1, bc1, true, SwFixed{(unsigned long long)kf}, &t2, &w2, &c2, hprow, horow,
-                    srow, C, list, hw2, hc2, sh);
+      f = sw_search<FT>(bw1, bc1, true, SwFixed{(unsigned long long)kf}, &t2, &w2, &c2, hprow, horow,
+                    srow, C, (uint32_t)list_cap, list, hw2, hc2, sh);
       wv = sw_weight(f.v);
       take = (unsigned long long)kf - f.ac;
     }
@@ -634,7 +674,7 @@ __global__ __launch_bounds__(SW_FT) void sw_finish_kernel(
   // ties at v: the `take` with the largest slots, i.e. those at or after tie_from
   uint32_t tie_from = take >= f.ntie ? 0u : (uint32_t)S_max;
   const auto slot = [](uint32_t p, int q) { return (uint32_t)q * SW_CH + (p & (SW_CH - 1)); };
-  if (take > 0 && take < f.ntie && S_max <= 32 * SW_FT) {
+  if (take > 0 && take < f.ntie && S_max <= 32 * FT) {
     // rows of up to 32768 slots: one pass sets the ties' bits in a slot bitmap (one word per
     // thread), a suffix count of the words from the top finds the word holding the cut, and
     // the cut inside it comes from registers
@@ -642,7 +682,7 @@ __global__ __launch_bounds__(SW_FT) void sw_finish_kernel(
     tb[tid] = 0u;
     __syncthreads();
     const uint32_t v = f.v;
-    sw_for_each<true>(f, list, sh, [&](uint32_t kk, uint32_t, uint32_t p, int q) {
+    sw_for_each<FT, true>(f, list, sh, [&](uint32_t kk, uint32_t, uint32_t p, int q) {
       if (kk == v) {
         const uint32_t j = slot(p, q);
         atomicOr(&tb[j >> 5], 1u << (j & 31));
@@ -660,7 +700,7 @@ __global__ __launch_bounds__(SW_FT) void sw_finish_kernel(
     __syncthreads();
     unsigned long long above = incl - cnt;
 #pragma unroll
-    for (int w = 0; w < SW_FW; ++w)
+    for (int w = 0; w < FT / 64; ++w)
       if (w < (tid >> 6)) above += sh.rc[w];
     if (above < take && above + cnt >= take) {
       // the (take - above)-th set bit from the top of this word
@@ -670,24 +710,24 @@ __global__ __launch_bounds__(SW_FT) void sw_finish_kernel(
     }
     __syncthreads();
     tie_from = sh.tie_from;
-  } else if (take > 0 && take < f.ntie) {
+  } else if (FT == SW_FT && take > 0 && take < f.ntie) {     // (short rows all take the bitmap)
     uint32_t* th = reinterpret_cast<uint32_t*>(hw2);     // ties per 128-slot block (<= 2048)
     th[2 * tid] = 0u;
     th[2 * tid + 1] = 0u;
     if (tid < 4) sh.tmask[tid] = 0u;
     __syncthreads();
     const uint32_t v = f.v;
-    sw_for_each<true>(f, list, sh, [&](uint32_t kk, uint32_t, uint32_t p, int q) {
+    sw_for_each<FT, true>(f, list, sh, [&](uint32_t kk, uint32_t, uint32_t p, int q) {
       if (kk == v) atomicAdd(&th[slot(p, q) >> SW_TSH], 1u);
     });
     __syncthreads();
     const unsigned long long bw[2] = {0ull, 0ull};
     const unsigned long long bc[2] = {th[2 * SW_FT - 1 - 2 * tid], th[2 * SW_FT - 2 - 2 * tid]};
     unsigned long long tg, tw, tc;
-    const SwPick pb = sw_pick<2, 2 * SW_FT>(bw, bc, true, SwFixed{take}, 0ull, 0ull, &tg, &tw, &tc, sh);
+    const SwPick pb = sw_pick<SW_FT, 2, 2 * SW_FT>(bw, bc, true, SwFixed{take}, 0ull, 0ull, &tg, &tw, &tc, sh);
     const uint32_t blk = pb.d;
     const uint32_t rem = (uint32_t)(take - pb.ac);     // ties to take inside block blk, >= 1
-    sw_for_each<true>(f, list, sh, [&](uint32_t kk, uint32_t, uint32_t p, int q) {
+    sw_for_each<FT, true>(f, list, sh, [&](uint32_t kk, uint32_t, uint32_t p, int q) {
       if (kk == v) {
         const uint32_t j = slot(p, q);
         if ((j >> SW_TSH) == blk) atomicOr(&sh.tmask[(j & 127) >> 5], 1u << (j & 31));
@@ -725,16 +765,17 @@ __global__ __launch_bounds__(SW_FT) void sw_finish_kernel(
 
 // One workgroup per (head, chunk): the chunk's words of the selection bitmap.
 __global__ __launch_bounds__(SW_NT) void sw_bitmap_kernel(
-    int S_max, int C, const unsigned long long* __restrict__ hp, const uint16_t* __restrict__ ho,
-    const uint32_t* __restrict__ sorted, const uint4* __restrict__ params,
-    uint32_t* __restrict__ sel_bits) {
+    int S_max, int C, int skip, const unsigned long long* __restrict__ hp,
+    const uint16_t* __restrict__ ho, const uint32_t* __restrict__ sorted, const uint4* __restrict__ params,
+    const int32_t* __restrict__ cand_len, uint32_t* __restrict__ sel_bits) {
   __shared__ uint32_t bits[SW_CH / 32];
   const int c = (int)blockIdx.x % C, h = (int)blockIdx.x / C, tid = threadIdx.x;
   if (tid < SW_CH / 32) bits[tid] = 0u;
   const uint4 p = params[h];
+  const bool live = c < sw_live(h, C, S_max, cand_len, skip);
   const uint32_t v = p.x, tie_from = p.y, d1 = p.z;
   __syncthreads();
-  if (v != SW_NONE) {
+  if (live && v != SW_NONE) {
     const size_t at = ((size_t)h * C + c) * SW_B1 + d1;
     const uint32_t off = ho[at], end = off + (uint32_t)(hp[at] >> SW_CNT_SH);
     const uint32_t* srow = sorted + (size_t)h * S_max + (size_t)c * SW_CH;
@@ -804,21 +845,32 @@ hipError_t hk_launch_select_wide(int n_heads, int S_max, const int32_t* cand_len
   uint4* params = reinterpret_cast<uint4*>(base + w.params);
   const int C = (S_max + SW_CH - 1) / SW_CH;
   const dim3 chunks(C * n_heads), block(SW_NT);
+  const int skip = (long long)C * n_heads > SW_RESIDENT;
   TimedLaunch t(n_metrics > 0 ? HK_TK_CALIB_TOPP : HK_TK_TOPP, st);
   if (n_metrics > 0) {
-    hipLaunchKernelGGL(sw_prep_kernel, chunks, block, 0, st, S_max, C, cand_len, mask, n_metrics,
+    hipLaunchKernelGGL(sw_prep_kernel, chunks, block, 0, st, S_max, C, skip, cand_len, mask, n_metrics,
                        x0, x1, T0, T1, part);
-    hipLaunchKernelGGL(sw_chunk_kernel<true>, chunks, block, 0, st, S_max, C, cand_len, mask,
+    hipLaunchKernelGGL(sw_chunk_kernel<true>, chunks, block, 0, st, S_max, C, skip, cand_len, mask,
                        n_metrics, x0, x1, T0, T1, w0, w1, part, c_in, c_out, lse_out, hp, ho,
                        sorted, status);
   } else {
-    hipLaunchKernelGGL(sw_chunk_kernel<false>, chunks, block, 0, st, S_max, C, cand_len, mask, 0,
+    hipLaunchKernelGGL(sw_chunk_kernel<false>, chunks, block, 0, st, S_max, C, skip, cand_len, mask, 0,
                        x0, x1, T0, T1, w0, w1, part, c_in, c_out, lse_out, hp, ho, sorted, status);
   }
-  allow_dynamic_lds<sw_finish_kernel>(SW_LDS);
-  hipLaunchKernelGGL(sw_finish_kernel, dim3(n_heads), dim3(SW_FT), SW_LDS, st, S_max, C, hp, ho,
-                     sorted, p_q, k_min, k_max, params, k_out, sel_mass);
-  hipLaunchKernelGGL(sw_bitmap_kernel, chunks, block, 0, st, S_max, C, hp, ho, sorted, params,
-                     sel_bits);
+  // the finishing workgroup's list never holds more keys than the row has slots: rows of up to
+  // SW_SHORT slots leave LDS for a second workgroup on the CU
+  const int list_cap = std::min(std::max((S_max + 63) & ~63, SW_LIST_MIN), SW_LIST);
+  const size_t lds = (size_t)list_cap * 4 + SW_B2 * 12;
+  if (S_max <= SW_SHORT && n_heads > 256) {
+    allow_dynamic_lds<sw_finish_kernel<SW_FS>>(lds);
+    hipLaunchKernelGGL(sw_finish_kernel<SW_FS>, dim3(n_heads), dim3(SW_FS), lds, st, S_max, C, skip, cand_len,
+                       list_cap, hp, ho, sorted, p_q, k_min, k_max, params, k_out, sel_mass);
+  } else {
+    allow_dynamic_lds<sw_finish_kernel<SW_FT>>(lds);
+    hipLaunchKernelGGL(sw_finish_kernel<SW_FT>, dim3(n_heads), dim3(SW_FT), lds, st, S_max, C, skip, cand_len,
+                       list_cap, hp, ho, sorted, p_q, k_min, k_max, params, k_out, sel_mass);
+  }
+  hipLaunchKernelGGL(sw_bitmap_kernel, chunks, block, 0, st, S_max, C, skip, hp, ho, sorted, params,
+                     cand_len, sel_bits);
   return hipGetLastError();
 }

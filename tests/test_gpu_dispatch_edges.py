@@ -96,3 +96,45 @@ def test_score_chunk_lengths(D, G, dtype, pages, lens, least):
         full[:len(ref_s)] = ref_s
         check_log_scores(sn[h], full, rtol, f"s head {h}")
         check_lse(ln[:, sq, kvh * G:(kvh + 1) * G].reshape(-1), ref_l, rtol, f"lse head {h}")
+
+
+# more workgroups than run at once: chunks past a row's candidates are skipped, and rows of up
+# to 12288 slots in more heads than CUs finish in 512-thread workgroups; row ends at, before
+# and past a 2048-slot chunk's edge, ties at the threshold
+@pytest.mark.parametrize("H,S", [(400, 12288), (300, 12320), (257, 16384), (700, 6176)])
+@pytest.mark.parametrize("ties", [False, True])
+def test_wide_select_skips_dead_chunks(H, S, ties):
+    import paper_2606_28831_amd as hk
+    gen = torch.Generator(device=DEV).manual_seed(H + S)
+    ends = torch.tensor([0, 1, 2047, 2048, 2049, 4096, S - 1, S, 16], device=DEV)
+    cl = ends[torch.arange(H, device=DEV) % len(ends)].to(torch.int32)
+    x = torch.randn((H, S), generator=gen, device=DEV) * 2
+    if ties:
+        x = x.round()
+    mask = torch.randint(-2 ** 15, 2 ** 15, (H, S // 16), generator=gen, device=DEV).to(torch.int16)
+    mask[:, ::3] = -1
+    new = lambda *s, dtype=torch.float32: torch.full(s, 7, dtype=dtype, device=DEV)
+    c1, c2, l1, l2 = new(H, S), new(H, S), new(H, 1), new(H, 1)
+    bits = [new(H, S // 32, dtype=torch.int32) for _ in range(2)]
+    k = [new(H, dtype=torch.int32) for _ in range(2)]
+    m = [new(H) for _ in range(2)]
+    ws = hk.select_workspace(H, S, DEV)
+    ws.fill_(255)
+    hk.hk_calibrate_topp_ws(H, S, cl, mask, [x], None, [1.0], 0.9, bits[0], k[0], ws, c_out=c1, lse_out=l1,
+                            sel_mass=m[0])
+    hk.hk_calibrate(H, S, cl, mask, [x], None, [1.0], c2, lse_out=l2)
+    torch.cuda.synchronize()
+    none = torch.isneginf(l2)
+    assert torch.equal(none, torch.isneginf(l1))
+    torch.testing.assert_close(l1[~none], l2[~none], rtol=1e-6, atol=2e-6)
+    torch.testing.assert_close(c1, c2, rtol=1e-5, atol=0)      # 2e-6 of a log-sum-exp near 10
+    # the selection of the c it computed, bit for bit, by the single-workgroup selector
+    hk.hk_topp_select(H, S, cl, mask, c1, 0.9, bits[1], k[1], sel_mass=m[1])
+    torch.cuda.synchronize()
+    assert torch.equal(bits[0], bits[1]) and torch.equal(k[0], k[1]) and torch.equal(m[0], m[1])
+    ws.fill_(255)
+    bits[0].fill_(7)
+    hk.hk_topp_select_ws(H, S, cl, mask, c1, 0.9, bits[0], k[0], ws, sel_mass=m[0], k_max=900)
+    hk.hk_topp_select(H, S, cl, mask, c1, 0.9, bits[1], k[1], sel_mass=m[1], k_max=900)
+    torch.cuda.synchronize()
+    assert torch.equal(bits[0], bits[1]) and torch.equal(k[0], k[1]) and torch.equal(m[0], m[1])
