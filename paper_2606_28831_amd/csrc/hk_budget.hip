@@ -14,6 +14,8 @@
 // row is thread j % NT's element j / NT, so a wave's 64 lanes cover 64 consecutive slots
 // (coalesced loads; one ballot gives two words of a bitmap).  A row's keys stay in
 // registers (at most 64 each).
+#include <type_traits>
+
 #include "hk_internal.h"
 
 namespace hk {
@@ -424,28 +426,113 @@ __device__ __forceinline__ void write_bitmap(uint64_t sel, uint32_t* __restrict_
 }
 
 // ------------------------------------------------------------------ Cautious Update votes
-// The head's page masks staged in LDS with every slot at or past cand_len cleared, for
-// all NT * EPT slots a workgroup covers (pages past S_max hold no candidates).
-template <int EPT, int NT>
-__device__ __forceinline__ void stage_cand_masks(int h, int S_max, const int32_t* __restrict__ cand_len,
-                                                 const uint16_t* __restrict__ mask, BgLds<NT>& sh) {
-  const int cl = min(cand_len[h], S_max);
-  const int np = S_max / HK_PAGE;
-  const uint16_t* mrow = mask ? mask + (size_t)h * np : nullptr;
-  for (int q = threadIdx.x; q < EPT * NT / HK_PAGE; q += NT) {
-    const int keep = min(max(cl - q * HK_PAGE, 0), HK_PAGE);
-    uint32_t m = (q < np && mrow) ? (uint32_t)mrow[q] : 0xffffu;
-    sh.mrow[q] = (uint16_t)(m & ((1u << keep) - 1u));
-  }
-  __syncthreads();
-}
+constexpr int VT_LIST = 512;           // keys of the boundary digit a wave keeps for later rounds
 
-// All ones when slot tid + NT * i is a candidate, else zero (masks staged as above).
 template <int NT>
-__device__ __forceinline__ uint32_t cand_lanes(const BgLds<NT>& sh, int i) {
+struct VtLds {
+  static constexpr int NW = NT / 64;
+  unsigned long long hist[RADIX_BINS];
+  uint32_t list[NW][VT_LIST];
+  uint16_t mrow[BG_EPT_MAX * NT / HK_PAGE];      // the head's page masks, cut at cand_len
+  unsigned long long red64[NW];
+  uint32_t redu[2][NW];
+  int redi[NW];
+  int tiecnt[BG_EPT_MAX * NW];
+  unsigned long long pick_above, pick_mass;
+  uint32_t pick_digit;
+  uint32_t only;
+};
+
+// All ones when slot tid + NT * i is a candidate, else zero (masks staged in sh.mrow).
+template <int NT>
+__device__ __forceinline__ uint32_t cand_lanes(const VtLds<NT>& sh, int i) {
   const int tid = threadIdx.x;
   const uint32_t m = sh.mrow[(tid >> 4) + (NT / HK_PAGE) * i];
   return (uint32_t)((int32_t)(m << (31 - (tid & 15))) >> 31);
+}
+
+// Inclusive prefix sum of a 64-bit value over the wave's lanes, or (ROWS false) over
+// each 16-lane row of them, on DPP lane moves.
+template <bool ROWS>
+__device__ __forceinline__ unsigned long long vt_scan(unsigned long long x) {
+  uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
+#define HK_SCAN_STEP(CTRL, RM)                                                                    \
+  {                                                                                               \
+    const unsigned long long t = ((unsigned long long)dpp_u32<CTRL, RM>(hi, 0u) << 32) |          \
+                                 dpp_u32<CTRL, RM>(lo, 0u);                                       \
+    const unsigned long long r = (((unsigned long long)hi << 32) | lo) + t;                       \
+    lo = (uint32_t)r;                                                                             \
+    hi = (uint32_t)(r >> 32);                                                                     \
+  }
+  HK_SCAN_STEP(0x111, 0xf)                 // row_shr:1, 2, 4, 8
+  HK_SCAN_STEP(0x112, 0xf)
+  HK_SCAN_STEP(0x114, 0xf)
+  HK_SCAN_STEP(0x118, 0xf)
+  if constexpr (ROWS) {
+    HK_SCAN_STEP(0x142, 0xa)               // row_bcast:15 into rows 1 and 3
+    HK_SCAN_STEP(0x143, 0xc)               // row_bcast:31 into rows 2 and 3
+  }
+#undef HK_SCAN_STEP
+  return ((unsigned long long)hi << 32) | lo;
+}
+__device__ __forceinline__ unsigned long long vt_lane(unsigned long long x, int lane) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane);
+  return ((unsigned long long)hi << 32) | lo;
+}
+
+// After a histogram round: the largest digit d with above + W(digits >= d) >= target, with
+// the weight above it (*above) and its own (*mass).  Thread t holds the digits BINS - 1 -
+// (BPT * t + b), which descend with the thread, so the weight above is a prefix.  On the
+// first round the target is target_of(the histogram's total) and comes back in *target; for a
+// target of 0 no digit is picked.
+template <int NT, typename TF>
+__device__ __forceinline__ uint32_t vt_pick(VtLds<NT>& sh, bool first, TF target_of,
+                                            unsigned long long* target, unsigned long long* above,
+                                            unsigned long long* mass) {
+  constexpr int NW = NT / 64, BPT = RADIX_BINS / NT;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  unsigned long long w[BPT], own = 0;
+#pragma unroll
+  for (int b = 0; b < BPT; ++b) {
+    w[b] = sh.hist[RADIX_BINS - 1 - (BPT * tid + b)];
+    own += w[b];
+  }
+  const unsigned long long incl = vt_scan<true>(own);
+  if (lane == 63) sh.red64[wave] = incl;
+  __syncthreads();
+  // the waves' sums, prefixed in the first lanes of every wave and read back as scalars
+  const unsigned long long pre = vt_scan<false>(sh.red64[lane & (NW - 1)]);
+  const int wv = __builtin_amdgcn_readfirstlane(wave);
+  unsigned long long cum = *above + incl - own;
+  if (wv > 0) cum += vt_lane(pre, wv - 1);
+  if (first) *target = target_of(vt_lane(pre, NW - 1));
+  const unsigned long long tg = *target;
+  if (tg == 0) return 0;
+  if (cum < tg && cum + own >= tg) {
+#pragma unroll
+    for (int b = 0; b < BPT; ++b) {
+      if (cum + w[b] >= tg) {
+        sh.pick_digit = (uint32_t)(RADIX_BINS - 1 - (BPT * tid + b));
+        sh.pick_above = cum;
+        sh.pick_mass = w[b];
+        break;
+      }
+      cum += w[b];
+    }
+  }
+  __syncthreads();
+  *above = vt_lane(sh.pick_above, 0);      // uniform: scalar from here on
+  *mass = vt_lane(sh.pick_mass, 0);
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.pick_digit);
+}
+
+template <int NT>
+__device__ __forceinline__ void vt_clear(VtLds<NT>& sh) {
+  __syncthreads();                   // earlier readers are done
+#pragma unroll
+  for (int b = 0; b < RADIX_BINS / NT; ++b) sh.hist[b * NT + threadIdx.x] = 0ull;
+  __syncthreads();
 }
 
 // v_writelane through its compiler intrinsic (which also keeps the wait states a
@@ -472,65 +559,96 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// Four waves per SIMD (two workgroups per CU) cap the registers at 128: the allocator
-// then keeps fewer loads in flight rather than lowering the occupancy.
+// One workgroup per (head, window row), the row's keys in registers.  A key is the value's bits
+// where the slot is a candidate and 0 elsewhere; only keys of 2^-40 and above weigh anything,
+// and the threshold is one of them, so the others stay out of the search, candidates or not.
+// (Only a row without any mass needs to know its candidates.)
+// The kernel is bound by VALU issue and by the histogram's LDS atomics, so everything a row
+// does per element is counted: rows without holes take no mask (slots past cand_len lie past
+// the buffer's end and read as 0), values below 2^-8 weigh one multiplication and one
+// conversion, the boundary digit's keys are appended to a list of the wave's own (no block
+// scan), and the bitmap needs one compare: the histogram's last bin tells whether ties at the
+// threshold have to be counted at all.  28672 rows of 32768 slots (3.76 GB): 1.25 ->
+// 0.98 ms (VALU instructions per element 46 -> 25).
 template <int NT, int EPT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 8))) void vote_topp_kernel(
     int R, int S_max, const int32_t* __restrict__ cand_len,
     const uint16_t* __restrict__ mask, const float* __restrict__ a_rows, int p_q,
     uint32_t* __restrict__ row_sel, int32_t* __restrict__ row_k, int32_t* __restrict__ status) {
   constexpr int BG_NW = NT / 64;
-  __shared__ BgLds<NT> sh;
-  constexpr uint32_t NONE = 0xffffffffu;  // key of a non-candidate
+  __shared__ VtLds<NT> sh;
   constexpr uint32_t ONE = 0x3f800000u;   // bits of 1.0f: in-range probabilities are <= ONE
+  constexpr uint32_t KW = 0x2b800000u;    // bits of 2^-40, the smallest key with a weight
   const int h = blockIdx.y, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   // one row per workgroup: a loop over rows would let the compiler keep per-element
   // addresses, masks and constants in registers across rows
   const int r = blockIdx.x;
-  stage_cand_masks<EPT>(h, S_max, cand_len, mask, sh);
-  // buffer loads: slots past the row's end read as 0 (they are no candidates), so no
-  // clamped addresses are needed
+  const int cl = max(0, min(cand_len[h], S_max));
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(a_rows + ((size_t)h * R + r) * S_max), (short)0, S_max * 4, 0x00020000);
+      (void*)(a_rows + ((size_t)h * R + r) * S_max), (short)0, cl * 4, 0x00020000);
   uint32_t key[EPT];
 #pragma unroll
   for (int i = 0; i < EPT; ++i)
     key[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, (tid + NT * i) * 4, 0, 0);
-  // a candidate keeps its bits, anything else takes the all-ones key; for non-negative
-  // floats the bit order is the value order
-  uint32_t kmin = NONE, kmax = 0u;
-#pragma unroll
-  for (int i = 0; i < EPT; ++i) {
-    const uint32_t m = cand_lanes(sh, i);
-    const uint32_t b = key[i] & m;
-    key[i] = b | ~m;
-    kmin = min(kmin, key[i]);
-    kmax = max(kmax, b);
+  // the head's page masks, cut at cand_len; holes: some slot below cand_len is no candidate
+  int hole = 0;
+  if (mask) {
+    const uint16_t* mrow = mask + (size_t)h * (S_max / HK_PAGE);
+    for (int q = tid; q < EPT * NT / HK_PAGE; q += NT) {
+      const uint32_t below = (1u << min(max(cl - q * HK_PAGE, 0), HK_PAGE)) - 1u;
+      const uint32_t m = below ? (uint32_t)mrow[q] & below : 0u;
+      sh.mrow[q] = (uint16_t)m;
+      hole |= m != below;
+    }
   }
-  block_key_range<uint32_t>(kmin, kmax, sh, &kmin, &kmax);
-  if (kmax > ONE) {
-    // some candidate is NaN, negative (-0 included) or above 1: clean every candidate
-    // (NaN -> 0, clamp to [0, 1], +0) and report what was found
-    int flags = 0;
-    kmin = NONE;
+  const bool holes = __syncthreads_or(hole);
+  if (holes) {
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) key[i] &= cand_lanes(sh, i);
+  }
+  // smallest weighing key (the others wrap around to large numbers), less KW; largest key
+  uint32_t kmin, kmax;
+  auto key_range = [&] {
+    kmin = 0xffffffffu;
     kmax = 0u;
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-      uint32_t k = NONE;
-      if (cand_lanes(sh, i)) {
-        float v = __uint_as_float(key[i]);    // a candidate's key holds its bits
-        if (v != v) { v = 0.f; flags |= HK_FLAG_NAN; }
-        if (v > 1.f) { v = 1.f; flags |= HK_FLAG_RANGE; }
-        if (v < 0.f) { v = 0.f; flags |= HK_FLAG_RANGE; }
-        if (v == 0.f) v = 0.f;                  // canonical +0
-        k = __float_as_uint(v);
-        kmin = min(kmin, k);
-        kmax = max(kmax, k);
-      }
-      key[i] = k;
+      kmin = min(kmin, key[i] - KW);
+      kmax = max(kmax, key[i]);
     }
-    block_key_range<uint32_t>(kmin, kmax, sh, &kmin, &kmax);
+    kmin = wave_reduce_u32(kmin, 0xffffffffu, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
+    kmax = wave_reduce_u32(kmax, 0u, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+    __syncthreads();
+    if (lane == 0) {
+      sh.redu[0][wave] = kmin;
+      sh.redu[1][wave] = kmax;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < BG_NW; ++w) {
+      kmin = min(kmin, sh.redu[0][w]);
+      kmax = max(kmax, sh.redu[1][w]);
+    }
+    kmin = (uint32_t)__builtin_amdgcn_readfirstlane((int)(kmin + KW));
+    kmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)kmax);
+  };
+  key_range();
+  if (kmax > ONE) {
+    // some candidate is NaN, negative (-0 included) or above 1: clean every key (NaN -> 0,
+    // clamp to [0, 1], +0) and report what was found
+    int flags = 0;
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+      float v = __uint_as_float(key[i]);
+      if (v != v) { v = 0.f; flags |= HK_FLAG_NAN; }
+      if (v > 1.f) { v = 1.f; flags |= HK_FLAG_RANGE; }
+      if (v < 0.f) { v = 0.f; flags |= HK_FLAG_RANGE; }
+      if (v == 0.f) v = 0.f;                  // canonical +0
+      key[i] = __float_as_uint(v);
+      asm volatile("" : "+v"(flags));         // one key at a time: the tests of 64 would spill
+    }
+    key_range();
     const int any_nan = __syncthreads_or(flags & HK_FLAG_NAN);
     const int any_range = __syncthreads_or(flags & HK_FLAG_RANGE);
     if (status && tid == 0 && (any_nan || any_range))
@@ -541,76 +659,183 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 8))) void
   const auto target_of = [pq](unsigned long long tot) {
     return pq * (tot / 1000000ull) + (pq * (tot % 1000000ull) + 999999ull) / 1000000ull;
   };
-  uint32_t v = NONE;
-  int take = 0;
-  if (kmin != NONE) {
-    unsigned long long target = 0, mass_gt = 0;
-    v = radix_threshold<EPT, uint32_t>(key, target_of, [](uint32_t k) { return mass_weight(k); },
-                                       kmin, kmax, sh, &target, &mass_gt);
-    if (target > 0) {
-      const unsigned long long wv = mass_weight(v);       // > 0: the crossing element weighs
-      take = (int)((target - mass_gt + wv - 1) / wv);
-    } else {
-      // no mass to reach: k_min = 1 keeps the largest value, the most recent on ties
-      v = kmax;
-      take = 1;
+  uint32_t* brow = row_sel + ((size_t)h * R + r) * (S_max / 32);
+  // The largest v with W(key >= v) >= target (0: no mass to reach), by radix: the bits above
+  // the highest one where the keys differ are common to all; below them, RADIX_BITS at a time.
+  uint32_t v = 0;
+  unsigned long long target = 0, above = 0, mass = 0;
+  if (kmax >= KW && kmin == kmax) {
+    int cnt = 0;
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) cnt += key[i] == kmax ? 1 : 0;
+    mass = (unsigned long long)block_sum_int<NT>(cnt, sh.redi) * mass_weight(kmax);
+    target = target_of(mass);
+    v = kmax;
+  } else if (kmax >= KW) {
+    int pos = highest_bit<uint32_t>(kmin ^ kmax) + 1;
+    uint32_t prefix = kmin & ~low_mask<uint32_t>(pos);
+    bool listed = false;
+    int n_w = 0;                     // keys in this wave's list
+    // the keys that share the digits found so far, each wave's into its own list
+    const auto stage = [&](int lo) {
+      const uint32_t top = prefix >> lo;
+      n_w = 0;
+#pragma unroll
+      for (int i = 0; i < EPT; ++i) {
+        const uint32_t k = key[i];
+        const bool in = (k >> lo) == top;
+        const uint64_t b = __ballot(in);
+        if (b) {
+          const int at = n_w + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+          if (in && at < VT_LIST) sh.list[wave][at] = k;
+          n_w += __popcll(b);
+        }
+      }
+      return !__syncthreads_or(n_w > VT_LIST);        // else the next round reads the registers
+    };
+    {
+      // first round: every weighing key shares the prefix; a digit's place in the histogram
+      // (8 bytes each) is the key rotated right by lo - 3 (or left), cut to the digit
+      const int nb = min(RADIX_BITS, pos), lo = pos - nb;
+      const uint32_t rot = (uint32_t)(lo - 3) & 31u, cut = ((1u << nb) - 1u) << 3;
+      const auto bin = [&](uint32_t k) {
+        return reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(sh.hist) +
+                                                     (__builtin_amdgcn_alignbit(k, k, rot) & cut));
+      };
+      vt_clear(sh);
+      if (kmax < 0x3b800000u) {      // all below 2^-8: the weight's high half is 0
+#pragma unroll
+        for (int i = 0; i < EPT; ++i)
+          if (key[i] >= KW)
+            atomicAdd(bin(key[i]), (unsigned long long)(uint32_t)(__uint_as_float(key[i]) * 1099511627776.0f));
+      } else {
+#pragma unroll
+        for (int i = 0; i < EPT; ++i)
+          if (key[i] >= KW) atomicAdd(bin(key[i]), mass_weight(key[i]));
+      }
+      __syncthreads();
+      const uint32_t d = vt_pick(sh, true, target_of, &target, &above, &mass);
+      prefix |= d << lo;
+      pos = target == 0 ? 0 : lo;
+      if (pos > 0) listed = stage(lo);
     }
+    while (pos > 0) {
+      const int nb = min(RADIX_BITS, pos), lo = pos - nb;
+      const uint32_t top = prefix >> pos, dmask = (1u << nb) - 1u;
+      vt_clear(sh);
+      if (listed) {
+        for (int j = lane; j < n_w; j += 64) {
+          const uint32_t k = sh.list[wave][j];
+          if ((k >> pos) == top) atomicAdd(&sh.hist[(k >> lo) & dmask], mass_weight(k));
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+          // (an opaque key keeps the compiler from hoisting the EPT weights out of the loop
+          // into registers of their own)
+          const uint32_t k = opaque(key[i]);
+          if (k >= KW && (k >> pos) == top) atomicAdd(&sh.hist[(k >> lo) & dmask], mass_weight(k));
+        }
+      }
+      __syncthreads();
+      const uint32_t d = vt_pick(sh, false, target_of, &target, &above, &mass);
+      prefix |= d << lo;
+      pos = lo;
+      if (pos > 0 && !listed) listed = stage(lo);
+      else if (pos > 0) {
+        // mostly one key value is left: then it is the threshold, without a last round
+        const uint32_t left = prefix >> pos;
+        for (int j = lane; j < n_w; j += 64) {
+          const uint32_t k = sh.list[wave][j];
+          if ((k >> pos) == left) sh.only = k;          // (any one of them)
+        }
+        __syncthreads();
+        const uint32_t one = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.only);
+        int other = 0;
+        for (int j = lane; j < n_w; j += 64) {
+          const uint32_t k = sh.list[wave][j];
+          other |= (k >> pos) == left && k != one;
+        }
+        if (!__syncthreads_or(other)) {
+          prefix = one;
+          pos = 0;
+        }
+      }
+    }
+    v = prefix;
+  }
+  int take = 0, tied = 0;            // tied: only `take` of the keys equal to v are kept
+  if (target > 0) {
+    // rest of the target that the keys equal to v (together `mass`) have to reach
+    const unsigned long long wv = mass_weight(v), rest = target - above;   // wv > 0
+    if (rest + wv <= mass) {
+      tied = 1;
+      take = (int)((rest + wv - 1) / wv);
+    }
+  } else if (kmax != 0) {
+    // nothing to reach: k_min = 1 keeps the largest value, the most recent on ties
+    v = kmax;
+    tied = 1;
+    take = 1;
+  } else {
+    // every candidate is 0: the most recent one, if there is any
+    int last = -1;
+    if (!holes) last = cl - 1;
+    else
+      for (int q = tid; q < EPT * NT / HK_PAGE; q += NT)
+        if (sh.mrow[q]) last = q * HK_PAGE + 31 - __clz((int)sh.mrow[q]);
+    last = (int)wave_reduce_u32((uint32_t)(last + 1), 0u, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+    __syncthreads();
+    if (lane == 0) sh.redi[wave] = last;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < BG_NW; ++w) last = max(last, sh.redi[w]);
+    last -= 1;
+    for (int q = tid; q < S_max / 32; q += NT) brow[q] = (last >> 5) == q && last >= 0 ? 1u << (last & 31) : 0u;
+    if (row_k && tid == 0) row_k[(size_t)h * R + r] = last >= 0 ? 1 : 0;
+    return;
   }
   v = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);     // uniform: from LDS
-  take = __builtin_amdgcn_readfirstlane(take);
   // The row's bitmap straight from ballots: lane i of a wave keeps the wave's ballot of
   // its element i (64 consecutive slots from NT * i + 64 * wave, two bitmap words) for
-  // the keys at or above the threshold; the wave's counts stay scalar.
+  // the keys at or above the threshold; the wave's count stays scalar.
   uint32_t ge_lo = 0, ge_hi = 0;
-  int n_ge = 0, n_eq = 0;
-  if (v != NONE) {
-    static_for<0, EPT>([&](auto ic) {
-      constexpr int i = decltype(ic)::value;
-      const uint32_t kk = opaque(key[i]);
-      const uint64_t bge = __ballot(kk - v < NONE - v);   // v <= kk < NONE
-      const uint64_t beq = __ballot(kk == v);
-      n_ge += __popcll(bge);
-      n_eq += __popcll(beq);
-      write_lane<i>(ge_lo, (uint32_t)bge);
-      write_lane<i>(ge_hi, (uint32_t)(bge >> 32));
-    });
-  }
-  __syncthreads();
-  if (lane == 0) {
-    sh.redi[wave] = n_ge;
-    sh.tiecnt[wave] = n_eq;
-  }
-  __syncthreads();
-  int n_tie = 0, n_above = 0;
-#pragma unroll
-  for (int w = 0; w < BG_NW; ++w) {
-    n_above += sh.redi[w];
-    n_tie += sh.tiecnt[w];
-  }
-  n_above -= n_tie;
-  const int k = n_above + min(take, n_tie);
-  if (take < n_tie) {
-    // only `take` (possibly 0) of the keys equal to v are kept: those at the largest slots.  The ballots
-    // are taken again: lane i of each wave keeps those of its element i, counts them in
-    // LDS, and a suffix sum in slot order (element, then wave) says how many lie above.
+  int n_ge = 0;
+  static_for<0, EPT>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    const uint64_t bge = __ballot(key[i] >= v);
+    n_ge += __popcll(bge);
+    write_lane<i>(ge_lo, (uint32_t)bge);
+    write_lane<i>(ge_hi, (uint32_t)(bge >> 32));
+    // four ballots in flight: more would spill the scalar registers
+    if constexpr (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  });
+  int n_drop = 0;
+  if (tied) {
+    // of the keys equal to v those at the largest slots are kept.  Lane i of each wave keeps
+    // the ballots of its element i, counts them in LDS, and a suffix sum in slot order
+    // (element, then wave) says how many lie above.
     uint32_t eq_lo = 0, eq_hi = 0;
     static_for<0, EPT>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
-      const uint64_t beq = __ballot(opaque(key[i]) == v);
+      const uint64_t beq = __ballot(key[i] == v);
       write_lane<i>(eq_lo, (uint32_t)beq);
       write_lane<i>(eq_hi, (uint32_t)(beq >> 32));
+      if constexpr (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     });
     __syncthreads();
     sh.tiecnt[lane * BG_NW + wave] = __popc(eq_lo) + __popc(eq_hi);
     __syncthreads();
     const int e = NT - 1 - tid;        // entries in descending slot order
     const int2 sc = block_exscan_bg<NT>(sh.tiecnt[e], sh.redi);
-    int* above = reinterpret_cast<int*>(sh.list);
-    above[e] = sc.x;
+    int* above_cnt = reinterpret_cast<int*>(sh.list);
+    above_cnt[e] = sc.x;
+    n_drop = max(0, sc.y - take);
     __syncthreads();
     uint64_t eq = ((uint64_t)eq_hi << 32) | eq_lo;
     const int cnt = __popcll(eq);
-    const int need = max(0, min(take - above[lane * BG_NW + wave], cnt));
+    const int need = max(0, min(take - above_cnt[lane * BG_NW + wave], cnt));
     for (int d = cnt - need; d > 0; --d) eq &= eq - 1;   // drop the lowest slots
     const uint64_t ge = ((uint64_t)ge_hi << 32) | ge_lo;
     const uint64_t eqall = ((uint64_t)eq_hi << 32) | eq_lo;
@@ -618,13 +843,22 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 8))) void
     ge_lo = (uint32_t)sel;
     ge_hi = (uint32_t)(sel >> 32);
   }
-  uint32_t* brow = row_sel + ((size_t)h * R + r) * (S_max / 32);
   const int j0 = NT * lane + 64 * wave;
   if (lane < EPT && j0 < S_max) {
     brow[j0 / 32] = ge_lo;
     if (j0 + 32 < S_max) brow[j0 / 32 + 1] = ge_hi;
   }
-  if (row_k && tid == 0) row_k[(size_t)h * R + r] = k;
+  if (row_k) {
+    __syncthreads();
+    if (lane == 0) sh.redi[wave] = n_ge;
+    __syncthreads();
+    if (tid == 0) {
+      int k = -n_drop;
+#pragma unroll
+      for (int w = 0; w < BG_NW; ++w) k += sh.redi[w];
+      row_k[(size_t)h * R + r] = k;
+    }
+  }
 }
 
 // votes[h][j] = sum over the R rows of bit j of row_sel[h][r]; one thread per 32-slot word.
@@ -709,21 +943,33 @@ __global__ __launch_bounds__(VC_NT) void vote_count_kernel(int R, int S_max,
 }
 
 // ------------------------------------------------------------------ budget state
-// One wave per head: used = 16 n_pages, valid = set mask bits.
-__global__ __launch_bounds__(256) void budget_plan_kernel(int n_heads, int max_pages,
-                                                          const int32_t* __restrict__ n_pages,
-                                                          const uint16_t* __restrict__ mask,
-                                                          int L_dense, int L_lower, int L_upper,
-                                                          int32_t* __restrict__ mode_out,
-                                                          int32_t* __restrict__ cap_out) {
-  const int h = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (h >= n_heads) return;
-  const int n = n_pages[h];
-  const uint16_t* mrow = mask + (size_t)h * max_pages;
+// One workgroup per head: used = 16 n_pages, valid = set mask bits.  (The table width is even,
+// so a row's masks are whole 32-bit words; one wave per head, a mask per load, took 11.6 us
+// for 128 heads of 2048 pages, four words in flight per thread 4.7.)
+constexpr int BP_NT = 256;
+__global__ __launch_bounds__(BP_NT) void budget_plan_kernel(int max_pages,
+                                                            const int32_t* __restrict__ n_pages,
+                                                            const uint16_t* __restrict__ mask,
+                                                            int L_dense, int L_lower, int L_upper,
+                                                            int32_t* __restrict__ mode_out,
+                                                            int32_t* __restrict__ cap_out) {
+  __shared__ int red[BP_NT / 64];
+  const int h = blockIdx.x;
+  const int n = n_pages[h], nw = max_pages / 2;
+  const uint32_t* words = reinterpret_cast<const uint32_t*>(mask + (size_t)h * max_pages);
   int valid = 0;
-  for (int pp = lane; pp < n; pp += 64) valid += __popc((uint32_t)mrow[pp]);
-  valid = wave_sum_i(valid);
-  if (lane == 0) {
+  for (int w0 = threadIdx.x; 2 * w0 < n; w0 += 4 * BP_NT) {
+    uint32_t m[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) m[u] = words[min(w0 + u * BP_NT, nw - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int left = n - 2 * (w0 + u * BP_NT);          // pages of the row from this word on
+      valid += __popc(left >= 2 ? m[u] : left == 1 ? m[u] & 0xffffu : 0u);
+    }
+  }
+  valid = block_sum_int<BP_NT>(valid, red);
+  if (threadIdx.x == 0) {
     const int nd = min(n, dense_pages(L_dense));
     int mode = HK_BUDGET_KEEP, cap = -1;
     if (HK_PAGE * (long long)n > L_upper) {
@@ -738,14 +984,24 @@ __global__ __launch_bounds__(256) void budget_plan_kernel(int n_heads, int max_p
 }
 
 // ------------------------------------------------------------------ budget selection
-template <int NT, int EPT>
+// RANK_C: keys are (votes, c); else the votes alone, in 32 bits, whose search is one round.
+// All of a thread's votes are loaded before any is used (behind the tests of an element each
+// load was waited on by itself).
+template <int NT, int EPT, bool RANK_C>
 __global__ __launch_bounds__(NT) void budget_select_kernel(
     int S_max, const int32_t* __restrict__ cand_len, const uint16_t* __restrict__ mask,
     const uint16_t* __restrict__ votes, const float* __restrict__ c, const uint32_t* __restrict__ sel_in,
     const int32_t* __restrict__ head_mode, const int32_t* __restrict__ k_cap, int n_sink,
     uint32_t* __restrict__ sel_out, int32_t* __restrict__ k_out) {
+  using K = std::conditional_t<RANK_C, uint64_t, uint32_t>;
   __shared__ BgLds<NT> sh;
   const int h = blockIdx.x, tid = threadIdx.x;
+  const uint16_t* vrow = votes ? votes + (size_t)h * S_max : nullptr;
+  const float* crow = c ? c + (size_t)h * S_max : nullptr;
+  const uint32_t* srow = sel_in ? sel_in + (size_t)h * (S_max / 32) : nullptr;
+  K key[EPT];                        // rank keys of the base set, all ones elsewhere
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) key[i] = vrow ? (K)vrow[min(tid + NT * i, S_max - 1)] : K(1);
   const uint64_t cf = cand_flags<EPT>(h, S_max, cand_len, mask, sh);
   const int mode = head_mode ? head_mode[h] : HK_BUDGET_REWRITE;
   uint32_t* brow = sel_out + (size_t)h * (S_max / 32);
@@ -755,34 +1011,36 @@ __global__ __launch_bounds__(NT) void budget_select_kernel(
     if (tid == 0) k_out[h] = n;
     return;
   }
-  const uint16_t* vrow = votes ? votes + (size_t)h * S_max : nullptr;
-  const float* crow = c ? c + (size_t)h * S_max : nullptr;
-  const uint32_t* srow = sel_in ? sel_in + (size_t)h * (S_max / 32) : nullptr;
   uint64_t sinks = 0, base = 0;
-  uint64_t key[EPT];                 // rank keys of the base set, all ones elsewhere
-  uint64_t kmin = ~0ull, kmax = 0ull;
-  // (per-element loads: a head's selection is one launch of n_heads workgroups, and
-  // loading all elements up front would not fit beside the 64-bit keys)
+  K kmin = ~K(0), kmax = K(0);
+  // (the other per-element loads stay behind the tests: loaded up front they would not fit
+  // beside the 64-bit keys)
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
     const int j = tid + NT * i;
-    key[i] = ~0ull;
+    const uint32_t vt = (uint32_t)key[i];
+    key[i] = ~K(0);
     if (!((cf >> i) & 1ull)) continue;
     if (j < n_sink) {
       sinks |= 1ull << i;
       continue;
     }
-    const uint32_t vt = vrow ? (uint32_t)vrow[j] : 0u;
-    if (vrow && vt == 0u) continue;
+    if (vt == 0u) continue;
     if (srow && !((srow[j >> 5] >> (j & 31)) & 1u)) continue;
-    float cv = crow ? crow[j] : 0.f;
-    if (cv != cv) cv = 0.f;
-    cv = fminf(fmaxf(cv, 0.f), 1.f);
-    if (cv == 0.f) cv = 0.f;                      // canonical +0
-    key[i] = ((uint64_t)vt << 32) | __float_as_uint(cv);
+    K k;
+    if constexpr (RANK_C) {
+      float cv = crow[j];
+      if (cv != cv) cv = 0.f;
+      cv = fminf(fmaxf(cv, 0.f), 1.f);
+      if (cv == 0.f) cv = 0.f;                      // canonical +0
+      k = ((uint64_t)(vrow ? vt : 0u) << 32) | __float_as_uint(cv);
+    } else {
+      k = vrow ? vt : 0u;
+    }
+    key[i] = k;
     base |= 1ull << i;
-    kmin = min(kmin, key[i]);
-    kmax = max(kmax, key[i]);
+    kmin = min(kmin, k);
+    kmax = max(kmax, k);
   }
   const int n_sinks = block_sum_int<NT>(__popcll(sinks), sh.redi);
   const int n_base = block_sum_int<NT>(__popcll(base), sh.redi);
@@ -792,18 +1050,18 @@ __global__ __launch_bounds__(NT) void budget_select_kernel(
   if (cap >= n_base) {
     sel |= base;
   } else if (cap > 0) {
-    block_key_range<uint64_t>(kmin, kmax, sh, &kmin, &kmax);
+    block_key_range<K>(kmin, kmax, sh, &kmin, &kmax);
     unsigned long long cnt_gt = 0, tgt = 0;
     const unsigned long long capu = (unsigned long long)cap;
-    const uint64_t v = radix_threshold<EPT, uint64_t>(
-        key, [capu](unsigned long long) { return capu; }, [](uint64_t) { return 1ull; }, kmin, kmax, sh,
+    const K v = radix_threshold<EPT, K>(
+        key, [capu](unsigned long long) { return capu; }, [](K) { return 1ull; }, kmin, kmax, sh,
         &tgt, &cnt_gt);
     const int take = cap - (int)cnt_gt;
     uint64_t tie = 0;
     const uint64_t fb = opaque(base);
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
-      const uint64_t k = opaque(key[i]);
+      const K k = opaque(key[i]);
       if ((fb >> i) & 1ull) {
         if (k > v) sel |= 1ull << i;
         if (k == v) tie |= 1ull << i;
@@ -859,8 +1117,12 @@ struct BudgetSelectLaunch {
                         const int32_t* head_mode, const int32_t* k_cap, int n_sink, uint32_t* sel_out,
                         int32_t* k_out, hipStream_t st) {
     TimedLaunch t(HK_TK_BUDGET_SELECT, st);
-    hipLaunchKernelGGL((budget_select_kernel<NT, EPT>), dim3(n_heads), dim3(NT), 0, st, S_max, cand_len,
-                       mask, votes, c, sel_in, head_mode, k_cap, n_sink, sel_out, k_out);
+    if (c)
+      hipLaunchKernelGGL((budget_select_kernel<NT, EPT, true>), dim3(n_heads), dim3(NT), 0, st, S_max,
+                         cand_len, mask, votes, c, sel_in, head_mode, k_cap, n_sink, sel_out, k_out);
+    else
+      hipLaunchKernelGGL((budget_select_kernel<NT, EPT, false>), dim3(n_heads), dim3(NT), 0, st, S_max,
+                         cand_len, mask, votes, c, sel_in, head_mode, k_cap, n_sink, sel_out, k_out);
     return hipGetLastError();
   }
 };
@@ -880,8 +1142,8 @@ hipError_t hk_launch_budget_plan(int n_heads, int max_pages, const int32_t* n_pa
                                  const uint16_t* mask, int L_dense, int L_lower, int L_upper,
                                  int32_t* head_mode, int32_t* k_cap, hipStream_t st) {
   TimedLaunch t(HK_TK_BUDGET_PLAN, st);
-  hipLaunchKernelGGL(budget_plan_kernel, dim3((n_heads + 3) / 4), dim3(256), 0, st, n_heads, max_pages,
-                     n_pages, mask, L_dense, L_lower, L_upper, head_mode, k_cap);
+  hipLaunchKernelGGL(budget_plan_kernel, dim3(n_heads), dim3(BP_NT), 0, st, max_pages, n_pages,
+                     mask, L_dense, L_lower, L_upper, head_mode, k_cap);
   return hipGetLastError();
 }
 
@@ -890,6 +1152,22 @@ hipError_t hk_launch_budget_select(int n_heads, int S_max, const int32_t* cand_l
                                    const uint32_t* sel_in, const int32_t* head_mode,
                                    const int32_t* k_cap, int n_sink, uint32_t* sel_out,
                                    int32_t* k_out, hipStream_t st) {
-  return by_ept<BudgetSelectLaunch>(S_max, n_heads, S_max, cand_len, mask, votes, c, sel_in, head_mode,
-                                    k_cap, n_sink, sel_out, k_out, st);
+  // One workgroup per head and the fewest elements per thread that cover the row; past 4096
+  // slots 1024 threads, which halve the chain of loads and list steps of 512 with twice the
+  // elements (128 heads x 32768 slots, no c: 103 us with 512 threads and 64-bit keys, 50 now).
+  const int e = S_max > 4096 ? (S_max + 1023) / 1024 : (S_max + 511) / 512;
+#define HK_SELECT(NT_, E_)                                                                          \
+  return BudgetSelectLaunch<NT_, E_>::run(n_heads, S_max, cand_len, mask, votes, c, sel_in, head_mode, \
+                                          k_cap, n_sink, sel_out, k_out, st)
+  if (S_max > 4096) {
+    if (e <= 8) HK_SELECT(1024, 8);
+    if (e <= 16) HK_SELECT(1024, 16);
+    if (e <= 32) HK_SELECT(1024, 32);
+    HK_SELECT(1024, 64);
+  }
+  if (e <= 1) HK_SELECT(512, 1);
+  if (e <= 2) HK_SELECT(512, 2);
+  if (e <= 4) HK_SELECT(512, 4);
+  HK_SELECT(512, 8);
+#undef HK_SELECT
 }

@@ -8,7 +8,7 @@ import torch
 
 import oracle as O
 import workload as WL
-from hk_testlib import RTOL, HostCache, check_lse, check_log_scores, check_prob, np64, q_rows
+from hk_testlib import RTOL, HostCache, check_lse, check_log_scores, check_prob, np64, q_rows, unpack_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -138,3 +138,56 @@ def test_wide_select_skips_dead_chunks(H, S, ties):
     hk.hk_topp_select(H, S, cl, mask, c1, 0.9, bits[1], k[1], sel_mass=m[1], k_max=900)
     torch.cuda.synchronize()
     assert torch.equal(bits[0], bits[1]) and torch.equal(k[0], k[1]) and torch.equal(m[0], m[1])
+
+
+def _vote_row(kind, n, rng):
+    if kind == "no_weight":                        # every value below 2^-40: nothing to reach
+        return np.exp2(-41.0 - rng.integers(0, 4, n)).astype(np.float32)
+    if kind == "around_weight":                    # both sides of 2^-40, the smallest weight
+        return np.exp2(-36.0 - 8.0 * rng.random(n)).astype(np.float32)
+    if kind == "peak":                             # one value of most of the mass, a long tail
+        a = np.exp2(-10.0 - 60.0 * rng.random(n)).astype(np.float32)
+        a[rng.integers(0, n)] = 0.75
+        return a
+    if kind == "binades":                          # both sides of 2^-8, where weights take a second half
+        return (np.exp2(-6.0 - 4.0 * rng.random(n))).astype(np.float32)
+    # one digit of the first round holds nearly every key (more than a wave's list), others far away
+    a = np.float32(2.0 ** -12) * (1.0 + rng.integers(0, 1 << 10, n) * np.float32(2.0 ** -22))
+    a[:: max(1, n // 40)] = 2.0 ** -30
+    a[0] = 0.5
+    return a.astype(np.float32)
+
+
+@pytest.mark.parametrize("S", [96, 8192, 32768, 40960])
+@pytest.mark.parametrize("kind", ["no_weight", "around_weight", "peak", "binades", "one_digit"])
+def test_vote_rows_weights_and_lists(kind, S):
+    import paper_2606_28831_amd as hk
+    rng = np.random.default_rng(S)
+    H, R, p = 4, 2, 0.9
+    cl = np.array([S, S - 5, S // 3, 0], np.int32)
+    mask = np.full((H, S // 16), 0xFFFF, np.int64)
+    mask[1, ::5] = 0x7FFE
+    a = np.empty((H, R, S), np.float32)
+    a[:, :, ::2], a[:, :, 1::2] = np.nan, 5.0      # what is no candidate is not looked at
+    cand = [O.candidate_mask(((mask[h][:, None] >> np.arange(16)) & 1).reshape(-1).astype(bool), int(cl[h]))
+            for h in range(H)]
+    for h in range(H):
+        for r in range(R):
+            if cand[h].any():
+                a[h, r, cand[h]] = _vote_row(kind, int(cand[h].sum()), rng)
+    votes = torch.full((H, S), 7, dtype=torch.int16, device=DEV)
+    row_sel = torch.full((H, R, S // 32), 7, dtype=torch.int32, device=DEV)
+    row_k = torch.empty(H, R, dtype=torch.int32, device=DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    hk.hk_vote_topp(H, R, S, torch.tensor(cl, device=DEV),
+                    torch.tensor(mask.astype(np.uint16).view(np.int16), device=DEV), torch.tensor(a, device=DEV), p,
+                    votes, row_sel, row_k=row_k, status=st)
+    torch.cuda.synchronize()
+    assert int(st.item()) == 0
+    got = row_sel.cpu().numpy()
+    for h in range(H):
+        ref_v, ref_k, ref_sel = O.vote_head(np.where(cand[h], a[h], 0), cand[h], p)
+        for r in range(R):
+            assert int(row_k[h, r]) == ref_k[r], (kind, h, r)
+            assert np.array_equal(unpack_bits(got[h, r], S), ref_sel[r]), (kind, h, r)
+        assert np.array_equal(votes[h].cpu().numpy().astype(np.int64) & 0xFFFF, ref_v), (kind, h)
