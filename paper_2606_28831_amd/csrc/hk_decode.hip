@@ -12,12 +12,14 @@
 // Each split stages its page ids and masks in LDS, and every wave keeps the next page's
 // loads in flight while it computes the current one.
 //
-// Lane mapping inside a wave, for one 16-slot page:
+// bf16 caches run on the matrix cores (decode_split_kernel); fp32 caches on the VALU, one page
+// per wave at a time (decode_split_f32_kernel), with this lane mapping:
 //   scores  lane = 4 * t + c: slot t, quarter c of the head dimension; partial dot
 //           products are summed over the 4 lanes of a slot with two xor-shuffles;
 //   values  lane = LPR * kg + dc: 16-byte chunk dc of the row, slots kg*KPL .. +KPL;
 //           the probabilities reach those lanes by shuffles.
 #include <mutex>
+#include <type_traits>
 
 #include "hk_internal.h"
 
@@ -37,13 +39,13 @@ __device__ __forceinline__ int decode_share(int n, int n_split, int pps) {
   return min(min(pps, DEC_PPS), max((n + n_split - 1) / n_split, DEC_PPS_MIN));
 }
 
-template <typename T, int D, int G>
-__global__ __launch_bounds__(DEC_NT) void decode_split_kernel(
-    const T* __restrict__ q, const T* __restrict__ k_pool, const T* __restrict__ v_pool,
+template <int D, int G>
+__global__ __launch_bounds__(DEC_NT) void decode_split_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k_pool, const float* __restrict__ v_pool,
     const int32_t* __restrict__ table, const uint16_t* __restrict__ masks,
     const int32_t* __restrict__ n_pages_arr, int Hq, int Hkv, int max_pages, float c2,
     float* __restrict__ part, int n_split, int pps) {
-  constexpr int ES = sizeof(T);
+  constexpr int ES = sizeof(float);
   constexpr int DQ = D / 4;                 // dims per quarter
   constexpr int VEC = 16 / ES;              // elements per 16-byte chunk
   constexpr int LPR = D / VEC;              // lanes per value row
@@ -133,16 +135,8 @@ __global__ __launch_bounds__(DEC_NT) void decode_split_kernel(
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       float z = 0.f;
-      if constexpr (ES == 2) {
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-        for (int i = 0; i < QW; ++i)
-          z = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q_word(qb, g, i)),
-                                              __builtin_bit_cast(bf16x2, kw[i]), z, false);
-      } else {
-#pragma unroll
-        for (int i = 0; i < QW; ++i) z = fmaf(__uint_as_float(q_word(qb, g, i)), __uint_as_float(kw[i]), z);
-      }
+      for (int i = 0; i < QW; ++i) z = fmaf(__uint_as_float(q_word(qb, g, i)), __uint_as_float(kw[i]), z);
       z += __shfl_xor(z, 1, 64);
       z += __shfl_xor(z, 2, 64);
       zl[g] = valid ? z * c2 : -INFINITY;      // log2 units
@@ -176,16 +170,8 @@ __global__ __launch_bounds__(DEC_NT) void decode_split_kernel(
       const int src_lane = 4 * (kg * KPL + i);
       float vf[VEC];
       const uint32_t vv[4] = {r.v[i].x, r.v[i].y, r.v[i].z, r.v[i].w};
-      if constexpr (ES == 2) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          vf[2 * e] = bf16_lo(vv[e]);
-          vf[2 * e + 1] = bf16_hi(vv[e]);
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) vf[e] = __uint_as_float(vv[e]);
-      }
+      for (int e = 0; e < 4; ++e) vf[e] = __uint_as_float(vv[e]);
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         const float pg = __shfl(pr[g], src_lane, 64);
@@ -225,6 +211,276 @@ __global__ __launch_bounds__(DEC_NT) void decode_split_kernel(
     if (lane < LPR)
 #pragma unroll
       for (int e = 0; e < VEC; ++e) s_o[wave][g][dc * VEC + e] = o[g][e];
+  }
+  __syncthreads();
+  // combine the waves -> one partial state per (head, split, g): [o(D) unnormalised, m, l]
+  for (int idx = threadIdx.x; idx < G * D; idx += DEC_NT) {
+    const int g = idx / D, d = idx % D;
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < DEC_NW; ++w) M = fmaxf(M, s_m[w][g]);
+    float L = 0.f, O = 0.f;
+    if (M != -INFINITY)
+#pragma unroll
+      for (int w = 0; w < DEC_NW; ++w) {
+        const float a = fast_exp2(s_m[w][g] - M);
+        L += s_l[w][g] * a;
+        O += s_o[w][g][d] * a;
+      }
+    float* dst = part + (((size_t)h * n_split + split) * G + g) * (D + 2);
+    dst[d] = O;
+    if (d == 0) {
+      dst[D] = M;
+      dst[D + 1] = L;
+    }
+  }
+}
+
+// ------------------------------------------------------------------ bf16 caches: matrix cores
+// The same split on MFMA 16x16x32, for any group of up to 8 query heads.  A wave takes two pages
+// (32 keys) at a time:
+//   scores  C[key][query] = K Q^T, one 16x16 tile per page: lane l supplies key l % 16 and dims
+//           32 s + 8 (l / 16) .. +8 of step s, and holds, of query l % 16, the keys 4 (l / 16) + r;
+//   values  C[query][dim] += P V: the contraction runs over the 32 keys in the order in which
+//           the score tiles leave them, so a lane's own 8 probabilities are its A operand and no
+//           probability crosses lanes.  A lane loads the 16-byte (D 64: 8-byte) piece l % 16 of
+//           the V rows of those 8 keys; two v_perm per pair of words turn rows into columns.
+// K of the next pair is requested as soon as the scores have read this pair's, V after its
+// columns are formed: one pair's registers, always full.  The usual pair needs no cross-lane
+// maximum: the running reference m moves only when a score exceeds it by 2^DEC_SLACK (the
+// merge takes any reference).
+// Precision.  P keeps its 24 bits: it is split exactly into three bf16 parts, whose products
+// with V are exact.  A pair's sum is formed by three MFMAs from zero and added to the running
+// sum by a rounded fp32 add.  The matrix cores cut sums downward, a bias that grew with the row
+// (3.4e-7 of the result at 65536 keys against 2.3e-7 for the VALU form): every other pair is
+// formed with the opposite sign and counted back, and a score is the sum of two shorter chains.
+// m is a whole number, so every rescaling factor of the state and of the merges is an exact
+// power of two.  Error of o against 64 bits, VALU form -> this: 1.77 -> 1.53e-7 (rows of 2000),
+// 2.41 -> 1.74e-7 (8192), 2.10 -> 1.91e-7 (23k to 33k), 2.31 -> 2.14e-7 (33k to 66k).
+// Bound by HBM reads.  The VALU form (two pages of prefetch, fdot2 and per-head fma) was
+// bound by issue from 7 heads on: 16 heads x 7 x 28k tokens 74 -> 43 us (with the merge),
+// 512 x 8 x 3000 218 -> 161, 512 x 4 x 8192 378 -> 370 (5.8 TB/s), 512 x 4 x 800-5600 172 -> 164,
+// 512 x 1 x 8192 unchanged at 359.
+constexpr float DEC_SLACK = 16.f;
+constexpr int DEC_GMAX = 8;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+template <int D>
+__global__ __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(3, 4))) void decode_split_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_pool, const uint16_t* __restrict__ v_pool,
+    const int32_t* __restrict__ table, const uint16_t* __restrict__ masks,
+    const int32_t* __restrict__ n_pages_arr, int G, int Hq, int Hkv, int max_pages, float c2,
+    float* __restrict__ part, int n_split, int pps) {
+  constexpr int KS = D / 32;                // MFMA steps over the head dimension
+  constexpr int VE = D / 16;                // dims of a V piece
+  constexpr int VW = VE / 2;                // 32-bit words of a V piece
+  using vpiece = std::conditional_t<VW == 4, u32x4, u32x2>;
+  __shared__ float s_m[DEC_NW][DEC_GMAX], s_l[DEC_NW][DEC_GMAX];
+  __shared__ __align__(16) float s_o[DEC_NW][DEC_GMAX][D];
+  __shared__ int32_t s_pid[DEC_PPS];
+  __shared__ uint16_t s_pm[DEC_PPS];
+
+  const int h = blockIdx.y, split = blockIdx.x;
+  const int s = h / Hkv, kv = h % Hkv;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = min(n_pages_arr[h], max_pages);
+  const int per = decode_share(n, n_split, pps);
+  const int p_begin = split * per, p_end = min(p_begin + per, n);
+  if (p_begin >= n) return;
+  const int cl = lane & 15, qd = lane >> 4;
+
+  // page ids and masks, staged once; past the range the last page again, with no valid slot
+  const int np = p_end - p_begin;
+  {
+    const int32_t* trow = table + (size_t)h * max_pages + p_begin;
+    const uint16_t* mrow = masks + (size_t)h * max_pages + p_begin;
+    for (int i = threadIdx.x; i < np; i += DEC_NT) {
+      s_pid[i] = trow[i];
+      s_pm[i] = mrow[i];
+    }
+  }
+  // the query rows as B operand: query cl, zero past the group
+  bf16x8 qf[KS];
+  {
+    const uint16_t* row = q + ((size_t)s * Hq + kv * G + min(cl, G - 1)) * D + qd * 8;
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      u32x4 u = *reinterpret_cast<const u32x4*>(row + i * 32);
+      if (cl >= G) u = u32x4{0u, 0u, 0u, 0u};
+      qf[i] = __builtin_bit_cast(bf16x8, u);
+    }
+  }
+  __syncthreads();
+
+  float m_run, l_run;                       // of query cl, this lane's keys
+  f32x4 acc[VE];                            // query 4 qd + r, dim VE cl + e
+  // this wave's pairs: pages 2 (wave + DEC_NW j) and the next, j < npair
+  const int pairs = (np + 1) >> 1;
+  const int npair = wave < pairs ? (pairs - 1 - wave) / DEC_NW + 1 : 0;
+  u32x4 kf[2][KS];
+  vpiece vf[8];
+  auto load_k = [&](int j) {
+    const int p0 = 2 * (wave + DEC_NW * min(j, npair - 1));
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const size_t page = (size_t)s_pid[min(p0 + t, np - 1)] * HK_PAGE;
+      const uint16_t* src = k_pool + (page + cl) * D + qd * 8;
+#pragma unroll
+      for (int i = 0; i < KS; ++i) kf[t][i] = *reinterpret_cast<const u32x4*>(src + i * 32);
+    }
+  };
+  auto load_v = [&](int j) {
+    const int p0 = 2 * (wave + DEC_NW * min(j, npair - 1));
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const size_t page = (size_t)s_pid[min(p0 + t, np - 1)] * HK_PAGE;
+      const uint16_t* src = v_pool + (page + 4 * qd) * D + cl * VE;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) vf[4 * t + i] = *reinterpret_cast<const vpiece*>(src + i * D);
+    }
+  };
+  // LEAD: the leading part of P in place of all three
+  auto walk = [&](auto lead) {
+    constexpr bool LEAD = decltype(lead)::value;
+    m_run = -INFINITY;
+    l_run = 0.f;
+#pragma unroll
+    for (int e = 0; e < VE; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (npair > 0) {
+      load_k(0);
+      load_v(0);
+    }
+    float sf = 1.f;                           // the sign this pair's products are formed with
+    for (int j = 0; j < npair; ++j) {
+      const float cs = sf * c2;
+      const int p0 = 2 * (wave + DEC_NW * j);
+      const uint32_t m32 = (uint32_t)s_pm[p0] | (p0 + 1 < np ? (uint32_t)s_pm[p0 + 1] << 16 : 0u);
+      f32x4 z[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        f32x4 half[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int i = 0; i < KS; ++i)
+          half[i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf[t][i]), qf[i],
+                                                                half[i & 1], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z[t][r] = half[0][r] + half[1][r];
+      }
+      load_k(j + 1);
+#pragma unroll
+      for (int i = 0; i < KS; ++i) qf[i] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, qf[i]) ^ 0x80008000u);
+      if (m32 != 0xffffffffu) {
+        const uint32_t mm = m32 >> (4 * qd);            // keys 4 qd + r: bits r and 16 + r
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (!((mm >> (16 * t + r)) & 1u)) z[t][r] = -INFINITY * sf;
+      }
+      float zx = z[0][0], zn = z[0][0];
+#pragma unroll
+      for (int k = 1; k < 8; ++k) {
+        zx = fmaxf(zx, z[k >> 2][k & 3]);
+        zn = fminf(zn, z[k >> 2][k & 3]);
+      }
+      float zm = (sf > 0.f ? zx : zn) * cs;             // the lane's largest, log2 units
+      if (__any(zm > m_run + DEC_SLACK)) {
+        // a new reference: the pair's maximum of each query (its four lanes l % 16 alike)
+        zm = fmaxf(zm, __shfl_xor(zm, 16, 64));
+        zm = fmaxf(zm, __shfl_xor(zm, 32, 64));
+        const float mn = fmaxf(m_run, ceilf(zm));
+        const float alpha = m_run == -INFINITY ? 0.f : fast_exp2(m_run - mn);
+        m_run = mn;
+        l_run *= alpha;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float ar = __shfl(alpha, 4 * qd + r, 64);
+#pragma unroll
+          for (int e = 0; e < VE; ++e) acc[e][r] *= ar;
+        }
+      }
+      // probabilities (0 where no key has come yet) and their three bf16 parts, two keys a word
+      const float mc = m_run == -INFINITY ? 0.f : m_run;
+      uint32_t ph[4], pm[4], pl[4];
+      float ps[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        uint32_t a[2], b[2], c[2];
+        ps[w] = 0.f;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int k = 2 * w + u;
+          float p = fast_exp2(fmaf(z[k >> 2][k & 3], cs, -mc));
+          ps[w] += p;
+          p *= sf;
+          a[u] = __float_as_uint(p);
+          const float r1 = p - __uint_as_float(a[u] & 0xffff0000u);
+          b[u] = __float_as_uint(r1);
+          c[u] = __float_as_uint(r1 - __uint_as_float(b[u] & 0xffff0000u));
+        }
+        ph[w] = __builtin_amdgcn_perm(a[1], a[0], 0x07060302u);
+        pm[w] = __builtin_amdgcn_perm(b[1], b[0], 0x07060302u);
+        pl[w] = __builtin_amdgcn_perm(c[1], c[0], 0x07060302u);
+      }
+      l_run += (ps[0] + ps[1]) + (ps[2] + ps[3]);
+      const bf16x8 fh = __builtin_bit_cast(bf16x8, u32x4{ph[0], ph[1], ph[2], ph[3]});
+      const bf16x8 fm = __builtin_bit_cast(bf16x8, u32x4{pm[0], pm[1], pm[2], pm[3]});
+      const bf16x8 fl = __builtin_bit_cast(bf16x8, u32x4{pl[0], pl[1], pl[2], pl[3]});
+#pragma unroll
+      for (int w = 0; w < VW; ++w) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const uint32_t sel = u ? 0x07060302u : 0x05040100u;
+          u32x4 b;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) b[i] = __builtin_amdgcn_perm(vf[2 * i + 1][w], vf[2 * i][w], sel);
+          const bf16x8 vb = __builtin_bit_cast(bf16x8, b);
+          f32x4 t = {0.f, 0.f, 0.f, 0.f};
+          if (!LEAD) {
+            t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl, vb, t, 0, 0, 0);
+            t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fm, vb, t, 0, 0, 0);
+          }
+          t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh, vb, t, 0, 0, 0);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[2 * w + u][r] = fmaf(t[r], sf, acc[2 * w + u][r]);
+        }
+      }
+      load_v(j + 1);
+      sf = -sf;
+    }
+  };
+  walk(std::false_type{});
+  float bad = 0.f;                          // NaN when some sum is not finite
+#pragma unroll
+  for (int e = 0; e < VE; ++e)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bad = fmaf(acc[e][r], 0.f, bad);
+  auto keep = [&](bool only_nan) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (4 * qd + r < G)
+#pragma unroll
+        for (int e = 0; e < VE; ++e) {
+          float* at = &s_o[wave][4 * qd + r][cl * VE + e];
+          if (!only_nan || *at != *at) *at = acc[e][r];
+        }
+  };
+  keep(false);
+  if (__any(bad != bad)) {
+    // An infinite value times a part of P that is 0 is NaN where value times P is infinite: the
+    // sums that came out NaN are taken from a second walk with the leading part alone.
+    if (npair & 1)                          // the queries' sign as at the start
+#pragma unroll
+      for (int i = 0; i < KS; ++i) qf[i] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, qf[i]) ^ 0x80008000u);
+    walk(std::true_type{});
+    keep(true);
+  }
+  // the four lanes of a query hold its sum in parts
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+  if (lane < G) {
+    s_m[wave][lane] = m_run;
+    s_l[wave][lane] = l_run;
   }
   __syncthreads();
   // combine the waves -> one partial state per (head, split, g): [o(D) unnormalised, m, l]
@@ -474,25 +730,33 @@ __global__ __launch_bounds__(AP_NT) void append_write_kernel(
   }
 }
 
-template <typename T, int D, int G>
-static void launch_split(dim3 grid, hipStream_t st, const void* q, const hk_paged_kv* kv, int Hq,
+template <int D>
+static void launch_split(int G, dim3 grid, hipStream_t st, const void* q, const hk_paged_kv* kv, int Hq,
                          int Hkv, float c2, float* part, int n_split, int pps) {
-  hipLaunchKernelGGL((decode_split_kernel<T, D, G>), grid, dim3(DEC_NT), 0, st,
-                     static_cast<const T*>(q), static_cast<const T*>(kv->k_pool),
-                     static_cast<const T*>(kv->v_pool), kv->page_table, kv->page_mask, kv->n_pages,
+  hipLaunchKernelGGL(decode_split_kernel<D>, grid, dim3(DEC_NT), 0, st, static_cast<const uint16_t*>(q),
+                     static_cast<const uint16_t*>(kv->k_pool), static_cast<const uint16_t*>(kv->v_pool),
+                     kv->page_table, kv->page_mask, kv->n_pages, G, Hq, Hkv, kv->max_pages, c2, part,
+                     n_split, pps);
+}
+
+template <int D, int G>
+static void launch_split_f32(dim3 grid, hipStream_t st, const void* q, const hk_paged_kv* kv, int Hq,
+                             int Hkv, float c2, float* part, int n_split, int pps) {
+  hipLaunchKernelGGL((decode_split_f32_kernel<D, G>), grid, dim3(DEC_NT), 0, st,
+                     static_cast<const float*>(q), static_cast<const float*>(kv->k_pool),
+                     static_cast<const float*>(kv->v_pool), kv->page_table, kv->page_mask, kv->n_pages,
                      Hq, Hkv, kv->max_pages, c2, part, n_split, pps);
 }
 
-template <typename T, int D>
-static bool launch_split_g(int G, dim3 grid, hipStream_t st, const void* q, const hk_paged_kv* kv,
-                           int Hq, int Hkv, float c2, float* part, int n_split, int pps) {
+template <int D>
+static void launch_split_f32_g(int G, dim3 grid, hipStream_t st, const void* q, const hk_paged_kv* kv,
+                               int Hq, int Hkv, float c2, float* part, int n_split, int pps) {
   switch (G) {
-    case 1: launch_split<T, D, 1>(grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps); return true;
-    case 2: launch_split<T, D, 2>(grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps); return true;
-    case 4: launch_split<T, D, 4>(grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps); return true;
-    case 7: launch_split<T, D, 7>(grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps); return true;
-    case 8: launch_split<T, D, 8>(grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps); return true;
-    default: return false;
+    case 1: launch_split_f32<D, 1>(grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps); break;
+    case 2: launch_split_f32<D, 2>(grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps); break;
+    case 4: launch_split_f32<D, 4>(grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps); break;
+    case 7: launch_split_f32<D, 7>(grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps); break;
+    default: launch_split_f32<D, 8>(grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps); break;
   }
 }
 
@@ -528,15 +792,14 @@ hipError_t hk_launch_decode(int NS, int Hq, int Hkv, int D, const void* q, const
   float* part = static_cast<float*>(ws);
   dim3 grid(n_split, n_heads);
   const bool bf = kv->dtype == HK_BF16;
-  bool ok;
+  if (!hk_decode_supports_group(G)) return hipErrorInvalidValue;
   {
-  TimedLaunch t(timed ? HK_TK_DECODE_SPLIT : -1, st);
-  if (bf && D == 128) ok = launch_split_g<uint16_t, 128>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps);
-  else if (bf) ok = launch_split_g<uint16_t, 64>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps);
-  else if (D == 128) ok = launch_split_g<float, 128>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps);
-  else ok = launch_split_g<float, 64>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps);
+    TimedLaunch t(timed ? HK_TK_DECODE_SPLIT : -1, st);
+    if (bf && D == 128) launch_split<128>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps);
+    else if (bf) launch_split<64>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps);
+    else if (D == 128) launch_split_f32_g<128>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps);
+    else launch_split_f32_g<64>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps);
   }
-  if (!ok) return hipErrorInvalidValue;
   TimedLaunch t(timed ? HK_TK_DECODE_MERGE : -1, st);
   const int n_q = n_heads * G;
 #define HK_MERGE(D_, NW_, U_)                                                                      \

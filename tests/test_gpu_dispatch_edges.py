@@ -191,3 +191,50 @@ def test_vote_rows_weights_and_lists(kind, S):
             assert int(row_k[h, r]) == ref_k[r], (kind, h, r)
             assert np.array_equal(unpack_bits(got[h, r], S), ref_sel[r]), (kind, h, r)
         assert np.array_equal(votes[h].cpu().numpy().astype(np.int64) & 0xFFFF, ref_v), (kind, h)
+
+
+# pairs of pages per wave: odd page counts, a last page alone, one slot, ranges that leave waves
+# without a pair; every group size; scores that climb by far more than 2^16 from page to page (a
+# new reference each time) and fall by as much
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("G", [1, 2, 4, 7, 8])
+def test_decode_bf16_page_pairs(D, G):
+    cfg = dict(L=1, B=6, Hq=G, Hkv=1, D=D, N=33 * 16, dtype="bf16", W=8, seed=47, recipe="normal")
+    _decode_against_oracle(cfg, [33 * 16, 16 * 16 + 1, 1, 17 * 16, 3 * 16 - 1, 0], 34)
+
+
+@pytest.mark.parametrize("G", [4, 7])
+def test_decode_bf16_extreme_scores(G):
+    import paper_2606_28831_amd as hk
+    D, pages, H = 128, 20, 4
+    cfg = dict(L=1, B=H, Hq=G, Hkv=1, D=D, N=pages * 16, dtype="bf16", W=8, seed=53, recipe="normal")
+    w = WL.make_workload(cfg, DEV, max_pages=pages)
+    n = pages * 16
+    step = torch.arange(n, device=DEV, dtype=torch.float32)
+    gain = torch.stack([step * 0.2, (n - step) * 0.2, torch.where(step % 37 == 0, 60.0, -60.0), step * 0])
+    u = torch.ones(D, device=DEV)
+    for h in range(H):
+        k = (torch.randn(n, D, device=DEV) * 0.1 + gain[h][:, None] * u / D ** 0.5).to(torch.bfloat16)
+        w.k_pool[w.page_table[h].long()] = k.view(pages, 16, D)
+    w.v_pool[w.page_table[3, 3].long(), 5, 7] = float("inf")      # a key of every weight but 0
+    kv = hk.PagedKV(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
+    d = hk.dims(H, G, 1, D)
+    q = (torch.randn(H, G, D, device=DEV) * 0.1 + u).to(torch.bfloat16)
+    o, lse = torch.empty(H, G, D, device=DEV), torch.empty(H, G, device=DEV)
+    hk.hk_decode_attn(d, q, kv, 1 / math.sqrt(D), o, lse, hk.workspace(hk.OP_DECODE, d, w.max_pages, DEV))
+    torch.cuda.synchronize()
+    host = HostCache(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
+    for h in range(H):
+        K, valid = host.head(h)
+        V, _ = host.head_v(h)
+        on = np64(o[h])
+        if h == 3:
+            assert np.all(np.isposinf(on[:, 7]))
+            V = np.where(np.isinf(V), 0.0, V)
+            on[:, 7] = 0.0
+        ref_o, ref_l = O.decode_head(np64(q[h]), K, V, valid, 1 / math.sqrt(D))
+        if h == 3:
+            ref_o[:, 7] = 0.0
+        for g in range(G):
+            check_prob(on[g], ref_o[g], RTOL["bf16"], f"o head {h} g {g}")
+        check_lse(np64(lse[h]), ref_l, RTOL["bf16"], f"lse head {h}")
