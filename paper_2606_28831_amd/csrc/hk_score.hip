@@ -181,16 +181,20 @@ static int score_ppw(int n_heads, int max_pages) {
 // pages), 64 x 256 296 -> 164 (64), 160 x 128 295 -> 279 (32), 200 x 128 stays at 128 (296; 64
 // pages 302).  Redundancy pass (set-up 48: it stages every reference row; whole score call,
 // 512 pages -> this rule): 8 heads x 1024 pages 194 -> 41 us, 32 x 1024 211 -> 98, 64 x 1024
-// 235 -> 176.
+// 235 -> 176.  Two cases keep the longest chunks, because the rows' lengths differ and then the
+// last round is shorter than counted while every set-up still adds up: a launch that gives
+// every CU a workgroup with them (552 heads of 295 to 470 pages with redundancy: 506 us, with
+// 256 pages 550), and one that would win less than a tenth (140 heads of 100 to 500 pages: 283
+// us, with 128 pages 291).
 static int score_ppw_rounds(int n_heads, int max_pages, int most, int least, int setup) {
+  const auto wgs = [&](int p) { return (long long)n_heads * ((max_pages + p - 1) / p); };
+  const auto cost = [&](int p) {
+    return (wgs(p) + SCORE_TARGET_WG - 1) / SCORE_TARGET_WG * (std::min(p, max_pages) + setup);
+  };
   int best = most;
-  long long cost = -1;
-  for (int p = most; p >= least; p >>= 1) {
-    const long long wg = (long long)n_heads * ((max_pages + p - 1) / p);
-    if (p < most && wg > SCORE_MAX_PARTS) break;
-    const long long c = (wg + SCORE_TARGET_WG - 1) / SCORE_TARGET_WG * (std::min(p, max_pages) + setup);
-    if (cost < 0 || c < cost) best = p, cost = c;
-  }
+  if (wgs(most) >= SCORE_TARGET_WG) return best;
+  for (int p = most >> 1; p >= least && wgs(p) <= SCORE_MAX_PARTS; p >>= 1)
+    if (cost(p) < cost(best) && 10 * cost(p) <= 9 * cost(most)) best = p;
   return best;
 }
 template <typename T>
@@ -1435,9 +1439,12 @@ hipError_t launch_score_q(const hk_score_args& a, hipStream_t st) {
   constexpr int R_pad = 32 * QB;
   const int n_heads = a.NS * a.Hkv;
   // pass 1 leaves one partial per (head, chunk, row) in the workspace: a workspace that only
-  // holds those of SCORE_PPW-page chunks gets such chunks
+  // holds those of SCORE_PPW-page chunks gets such chunks.  So does a call with the redundancy
+  // metric: other chunks round the row LSEs otherwise in the last bit, and beside the
+  // temperature that is solved from these scores that moved a slot across the Top-p threshold
+  // in 6 of 100 calls of few heads (1.5 of 100 without that metric).
   const int ppw2 = score_ppw_t<T>(n_heads, kv->max_pages);
-  const int ppw = a.row_lse_in || a.ws_bytes >= score_ws(n_heads, (kv->max_pages + ppw2 - 1) / ppw2, R_pad, a.W * a.NS * a.Hq)
+  const int ppw = a.row_lse_in || (!a.x_red && a.ws_bytes >= score_ws(n_heads, (kv->max_pages + ppw2 - 1) / ppw2, R_pad, a.W * a.NS * a.Hq))
                       ? ppw2 : SCORE_PPW;
   const int n_chunks = (kv->max_pages + ppw - 1) / ppw;
   const float c2 = a.sm_scale * kLog2e;

@@ -238,3 +238,42 @@ def test_decode_bf16_extreme_scores(G):
         for g in range(G):
             check_prob(on[g], ref_o[g], RTOL["bf16"], f"o head {h} g {g}")
         check_lse(np64(lse[h]), ref_l, RTOL["bf16"], f"lse head {h}")
+
+
+# A call with the redundancy metric keeps 128-page chunks in pass 1 (its row LSEs, and with them
+# the log scores, are those of the least workspace bit for bit), while its second pass takes
+# shorter chunks with few heads (2 x 2) and 512-page ones where every CU has a workgroup (64 x 4).
+@pytest.mark.parametrize("NS,Hkv,pages", [(2, 2, 520), (64, 4, 34)])
+def test_redundancy_chunk_lengths(NS, Hkv, pages):
+    import paper_2606_28831_amd as hk
+    D, G, W, n_ref = 64, 2, 8, 33
+    H, least = NS * Hkv, pages * 16 - 40
+    lens = [pages * 16 - 8 * (i % 6) for i in range(H)]
+    cfg = dict(L=1, B=NS, Hq=Hkv * G, Hkv=Hkv, D=D, N=pages * 16, dtype="bf16", W=W, seed=47, recipe="normal")
+    w = WL.make_workload(cfg, DEV, head_lens=lens, max_pages=pages)
+    kv = hk.PagedKV(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
+    d = hk.dims(NS, Hkv * G, Hkv, D, W)
+    full = hk.workspace(hk.OP_SCORE, d, w.max_pages, DEV)
+    small = -(-H * -(-w.max_pages // 128) * 32 * 8 // 256) * 256 + -(-W * NS * Hkv * G * 4 // 256) * 256
+    ref = (torch.arange(n_ref, device=DEV, dtype=torch.int32) * (least // n_ref)).expand(H, n_ref).contiguous()
+    out = []
+    for ws in (full, full[:small]):
+        s, x = (torch.full((H, w.S_max), 7.0, device=DEV) for _ in "sx")
+        cl, lse = torch.empty(H, dtype=torch.int32, device=DEV), torch.empty(W, NS, Hkv * G, device=DEV)
+        hk.hk_score(d, w.q_obs, kv, 48, 1 / math.sqrt(D), s, cl, row_lse_out=lse, ref_slots=ref, n_ref=n_ref, x_red=x,
+                    ws=ws)
+        out.append((s, lse, x))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    x = np64(out[0][2])
+    host = HostCache(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
+    for h in (0, H - 1):
+        K, valid = host.head(h)
+        n = 16 * (int(w.n_pages[h]) - 3)
+        K = np.asarray(K, np.float64) / np.linalg.norm(K, axis=1, keepdims=True).clip(1e-30)
+        r = ref[h].cpu().numpy()
+        cos = K[:n] @ K[r].T
+        cos[r[r < n], np.nonzero(r < n)[0]] = -np.inf
+        # bf16 products are exact, fp32 sums over D and an fp32 norm: 1e-5 absolute on a cosine
+        assert np.abs(x[h, :n] + cos.max(1))[valid[:n].astype(bool)].max() < 1e-5
+        assert np.isneginf(x[h, n:]).all()
