@@ -339,9 +339,11 @@ __global__ __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(3, 4))) 
       for (int i = 0; i < 4; ++i) vf[4 * t + i] = *reinterpret_cast<const vpiece*>(src + i * D);
     }
   };
-  // LEAD: the leading part of P in place of all three
-  auto walk = [&](auto lead) {
-    constexpr bool LEAD = decltype(lead)::value;
+  // COLD: the walk again, where a sum came out NaN or too large: a new reference with every
+  // larger score (no probability above 1), and with `lead` the leading part of P for all three
+  auto walk = [&](auto cold, bool lead) {
+    constexpr bool COLD = decltype(cold)::value;
+    constexpr float SLACK = COLD ? 0.f : DEC_SLACK;
     m_run = -INFINITY;
     l_run = 0.f;
 #pragma unroll
@@ -384,7 +386,7 @@ __global__ __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(3, 4))) 
         zn = fminf(zn, z[k >> 2][k & 3]);
       }
       float zm = (sf > 0.f ? zx : zn) * cs;             // the lane's largest, log2 units
-      if (__any(zm > m_run + DEC_SLACK)) {
+      if (__any(zm > m_run + SLACK)) {
         // a new reference: the pair's maximum of each query (its four lanes l % 16 alike)
         zm = fmaxf(zm, __shfl_xor(zm, 16, 64));
         zm = fmaxf(zm, __shfl_xor(zm, 32, 64));
@@ -436,7 +438,7 @@ __global__ __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(3, 4))) 
           for (int i = 0; i < 4; ++i) b[i] = __builtin_amdgcn_perm(vf[2 * i + 1][w], vf[2 * i][w], sel);
           const bf16x8 vb = __builtin_bit_cast(bf16x8, b);
           f32x4 t = {0.f, 0.f, 0.f, 0.f};
-          if (!LEAD) {
+          if (!COLD || !lead) {
             t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl, vb, t, 0, 0, 0);
             t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fm, vb, t, 0, 0, 0);
           }
@@ -449,12 +451,12 @@ __global__ __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(3, 4))) 
       sf = -sf;
     }
   };
-  walk(std::false_type{});
-  float bad = 0.f;                          // NaN when some sum is not finite
+  walk(std::false_type{}, false);
+  float bad = 0.f;                          // NaN when some sum is NaN or 2^104 or above
 #pragma unroll
   for (int e = 0; e < VE; ++e)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) bad = fmaf(acc[e][r], 0.f, bad);
+    for (int r = 0; r < 4; ++r) bad = fmaf(acc[e][r] * 0x1p24f, 0.f, bad);
   auto keep = [&](bool only_nan) {
 #pragma unroll
     for (int r = 0; r < 4; ++r)
@@ -467,13 +469,18 @@ __global__ __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(3, 4))) 
   };
   keep(false);
   if (__any(bad != bad)) {
-    // An infinite value times a part of P that is 0 is NaN where value times P is infinite: the
-    // sums that came out NaN are taken from a second walk with the leading part alone.
-    if (npair & 1)                          // the queries' sign as at the start
+    // Values near the end of the fp32 range overflow, here or where the states are merged,
+    // against a reference that lies below the largest score: the walk is done again with
+    // references that no score exceeds.  An infinite value times a part of P that is 0 is NaN
+    // where value times P is infinite: sums that are NaN after that walk are taken from a third
+    // one with the leading part alone.
+    for (int lead = 0; lead < 2; ++lead) {
+      if (npair & 1)                        // the queries' sign as at the start
 #pragma unroll
-      for (int i = 0; i < KS; ++i) qf[i] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, qf[i]) ^ 0x80008000u);
-    walk(std::true_type{});
-    keep(true);
+        for (int i = 0; i < KS; ++i) qf[i] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, qf[i]) ^ 0x80008000u);
+      walk(std::true_type{}, lead);
+      keep(lead);
+    }
   }
   // the four lanes of a query hold its sum in parts
   l_run += __shfl_xor(l_run, 16, 64);

@@ -240,6 +240,40 @@ def test_decode_bf16_extreme_scores(G):
         check_lse(np64(lse[h]), ref_l, RTOL["bf16"], f"lse head {h}")
 
 
+# Values near the end of the fp32 range: their sums hold against the largest score of a row, also
+# where that score comes late and lies above the earlier ones by less than 2^16; beside them a head
+# of ordinary values.
+@pytest.mark.parametrize("D,G", [(64, 7), (128, 4)])
+def test_decode_bf16_large_values(D, G):
+    import paper_2606_28831_amd as hk
+    pages, H = 20, 3
+    cfg = dict(L=1, B=H, Hq=G, Hkv=1, D=D, N=pages * 16, dtype="bf16", W=8, seed=59, recipe="normal")
+    w = WL.make_workload(cfg, DEV, max_pages=pages)
+    n = pages * 16
+    gen = torch.Generator(device=DEV).manual_seed(59)
+    late = torch.zeros(n, device=DEV)
+    late[139:] = 10.0                                   # e^10 = 2^14.4 times the weight of the others
+    for h, big in enumerate([2.0 ** 118, 2.0 ** 110, 1.0]):
+        k = (torch.randn(n, D, generator=gen, device=DEV) * 0.05 + late[:, None] / D).to(torch.bfloat16)
+        v = (big * (1.0 + torch.rand(n, D, generator=gen, device=DEV))).to(torch.bfloat16)
+        w.k_pool[w.page_table[h].long()] = k.view(pages, 16, D)
+        w.v_pool[w.page_table[h].long()] = v.view(pages, 16, D)
+    kv = hk.PagedKV(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
+    d = hk.dims(H, G, 1, D)
+    q = torch.ones(H, G, D, device=DEV).to(torch.bfloat16)
+    o, lse = torch.empty(H, G, D, device=DEV), torch.empty(H, G, device=DEV)
+    hk.hk_decode_attn(d, q, kv, 1.0, o, lse, hk.workspace(hk.OP_DECODE, d, w.max_pages, DEV))
+    torch.cuda.synchronize()
+    host = HostCache(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
+    for h in range(H):
+        K, valid = host.head(h)
+        V, _ = host.head_v(h)
+        ref_o, ref_l = O.decode_head(np64(q[h]), K, V, valid, 1.0)
+        for g in range(G):
+            check_prob(np64(o[h])[g], ref_o[g], RTOL["bf16"], f"o head {h} g {g}")
+        check_lse(np64(lse[h]), ref_l, RTOL["bf16"], f"lse head {h}")
+
+
 # A call with the redundancy metric keeps 128-page chunks in pass 1 (its row LSEs, and with them
 # the log scores, are those of the least workspace bit for bit), while its second pass takes
 # shorter chunks with few heads (2 x 2) and 512-page ones where every CU has a workgroup (64 x 4).
