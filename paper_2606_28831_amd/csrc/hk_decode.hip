@@ -428,6 +428,9 @@ __global__ __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(3, 4))) 
       const bf16x8 fh = __builtin_bit_cast(bf16x8, u32x4{ph[0], ph[1], ph[2], ph[3]});
       const bf16x8 fm = __builtin_bit_cast(bf16x8, u32x4{pm[0], pm[1], pm[2], pm[3]});
       const bf16x8 fl = __builtin_bit_cast(bf16x8, u32x4{pl[0], pl[1], pl[2], pl[3]});
+      if (COLD && p0 + 1 >= np)               // the last page repeated: no infinity times its 0
+#pragma unroll
+        for (int i = 4; i < 8; ++i) vf[i] = vpiece{};
 #pragma unroll
       for (int w = 0; w < VW; ++w) {
 #pragma unroll

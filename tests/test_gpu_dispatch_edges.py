@@ -274,6 +274,40 @@ def test_decode_bf16_large_values(D, G):
         check_lse(np64(lse[h]), ref_l, RTOL["bf16"], f"lse head {h}")
 
 
+# Infinite values give infinite sums, also in the last page of an odd number of pages (which the
+# pair of pages repeats with an empty mask), beside sums that stay finite and ones that are large.
+@pytest.mark.parametrize("D,G", [(64, 1), (128, 7)])
+@pytest.mark.parametrize("n_pages", [1, 2, 5, 7, 15, 17, 33])
+def test_decode_bf16_infinite_values_last_page(D, G, n_pages):
+    import paper_2606_28831_amd as hk
+    H, n = 2, n_pages * 16 - 3                          # the last page holds 13 slots
+    cfg = dict(L=1, B=H, Hq=G, Hkv=1, D=D, N=n, dtype="bf16", W=8, seed=61, recipe="normal")
+    w = WL.make_workload(cfg, DEV, head_lens=[n, n], max_pages=34)
+    last = w.page_table[:, n_pages - 1].long()
+    w.v_pool[last, 4, 7] = float("inf")
+    w.v_pool[last[0], 12, 9] = float("-inf")
+    w.v_pool[last[1], 2, 11] = 2.0 ** 126
+    kv = hk.PagedKV(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
+    d = hk.dims(H, G, 1, D)
+    gen = torch.Generator(device=DEV).manual_seed(61)
+    q = torch.randn(H, G, D, generator=gen, device=DEV).to(torch.bfloat16)
+    o, lse = torch.empty(H, G, D, device=DEV), torch.empty(H, G, device=DEV)
+    hk.hk_decode_attn(d, q, kv, 1 / math.sqrt(D), o, lse, hk.workspace(hk.OP_DECODE, d, w.max_pages, DEV))
+    torch.cuda.synchronize()
+    host = HostCache(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
+    for h in range(H):
+        K, valid = host.head(h)
+        V, _ = host.head_v(h)
+        on, inf = np64(o[h]), np.isinf(V).any(0)
+        assert np.all(np.isposinf(on[:, 7])) and (h == 1 or np.all(np.isneginf(on[:, 9])))
+        ref_o, ref_l = O.decode_head(np64(q[h]), K, np.where(np.isinf(V), 0.0, V), valid, 1 / math.sqrt(D))
+        large = np.abs(ref_o[0]) > 1e30                  # its own scale: the others are near 1
+        for g in range(G):
+            check_prob(on[g][~inf & ~large], ref_o[g][~inf & ~large], RTOL["bf16"], f"o head {h} g {g}")
+            check_prob(on[g][large], ref_o[g][large], RTOL["bf16"], f"large o head {h} g {g}")
+        check_lse(np64(lse[h]), ref_l, RTOL["bf16"], f"lse head {h}")
+
+
 # A call with the redundancy metric keeps 128-page chunks in pass 1 (its row LSEs, and with them
 # the log scores, are those of the least workspace bit for bit), while its second pass takes
 # shorter chunks with few heads (2 x 2) and 512-page ones where every CU has a workgroup (64 x 4).
