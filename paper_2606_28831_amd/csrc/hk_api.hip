@@ -58,8 +58,7 @@ size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 // selection and compaction scratch (the stages run one after the other; they share one
 // region).
 struct CompressWs {
-  size_t s, cand, lse, sel, scratch;
-  size_t total, least;     // what hk_workspace_size asks for, and the least the call runs with
+  size_t s, cand, lse, sel, scratch, total;
 };
 CompressWs compress_ws(const hk_dims* d, int max_pages) {
   const size_t H = (size_t)d->NS * d->Hkv, S = (size_t)max_pages * HK_PAGE;
@@ -70,11 +69,9 @@ CompressWs compress_ws(const hk_dims* d, int max_pages) {
   w.sel = w.lse + al256((size_t)d->W * d->NS * d->Hq * 4);
   w.scratch = w.sel + al256(H * (S / 32) * 4);
   const size_t a = hk_score_ws(d->NS, d->Hq, d->Hkv, d->W, max_pages);
-  const size_t a_min = hk_score_ws_min(d->NS, d->Hq, d->Hkv, d->W, max_pages);
   const size_t b = hk_compact_ws((int)H, max_pages);
   const size_t c = hk_select_wide_ws((int)H, (int)S);
   w.total = w.scratch + al256(std::max(a, std::max(b, c)));
-  w.least = w.scratch + al256(std::max(a_min, std::max(b, c)));
   return w;
 }
 
@@ -137,7 +134,7 @@ hk_status hk_score(const hk_dims* dims, const void* q_obs, const hk_paged_kv* kv
   if (hk_score_lds_bytes(dims->Hq / dims->Hkv * dims->W, dims->D, kv->dtype == HK_BF16 ? 2 : 4,
                          x_red != nullptr) > 160 * 1024)
     return HK_ERR_SHAPE;
-  const size_t need = hk_score_ws_min(dims->NS, dims->Hq, dims->Hkv, dims->W, kv->max_pages);
+  const size_t need = hk_score_ws(dims->NS, dims->Hq, dims->Hkv, dims->W, kv->max_pages);
   if (!row_lse_in) {
     if (!workspace || ws_bytes < need) return HK_ERR_WORKSPACE;
     if (!aligned256(workspace)) return HK_ERR_ALIGN;
@@ -160,7 +157,6 @@ hk_status hk_score(const hk_dims* dims, const void* q_obs, const hk_paged_kv* kv
   a.n_ref = x_red ? n_ref : 0;
   a.x_red = x_red;
   a.ws = workspace;
-  a.ws_bytes = ws_bytes;
   return launched(hk_launch_score(a, stream));
 }
 
@@ -337,7 +333,7 @@ hk_status hk_compress(const hk_dims* dims, const void* q_obs, const hk_paged_kv*
   // the selection's row limits, checked here so that no launch runs before a refusal
   if (kv->max_pages > kMaxSlotsWide / HK_PAGE || dims->NS * dims->Hkv > (1 << 20)) return HK_ERR_SHAPE;
   const CompressWs cw = compress_ws(dims, kv->max_pages);
-  if (ws_bytes < cw.least) return HK_ERR_WORKSPACE;
+  if (ws_bytes < cw.total) return HK_ERR_WORKSPACE;
   if (!aligned256(workspace)) return HK_ERR_ALIGN;
   if (sel_bits_out && !aligned16(sel_bits_out)) return HK_ERR_ALIGN;
   char* ws = static_cast<char*>(workspace);

@@ -194,12 +194,9 @@ struct hk_score_args {
   int n_ref;
   float* x_red;
   void* ws;
-  size_t ws_bytes;
 };
 hipError_t hk_launch_score(const hk_score_args& a, hipStream_t st);
-// workspace of hk_score: what it asks for, and the least it runs with
 size_t hk_score_ws(int NS, int Hq, int Hkv, int W, int max_pages);
-size_t hk_score_ws_min(int NS, int Hq, int Hkv, int W, int max_pages);
 size_t hk_score_lds_bytes(int R, int D, int esize, bool redundancy);
 hipError_t hk_launch_score_rows(int NS, int Hq, int Hkv, int D, int W, const void* q_obs,
                                 const hk_paged_kv* kv, int L_dense, float sm_scale,

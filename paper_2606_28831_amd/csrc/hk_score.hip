@@ -151,7 +151,6 @@ constexpr int SCORE_NW = SCORE_NT / 64;
 constexpr int SCORE_PPW = 128;             // most pages per workgroup
 constexpr int SCORE_PPW_MIN = 16;          // fewest: one 32-key tile per wave
 constexpr int SCORE_TARGET_WG = 256;       // workgroups a pass should offer: one per CU
-constexpr int SCORE_MAX_PARTS = 4096;      // most workgroups a launch with shorter chunks takes
 constexpr int SCORE_KT = 1;                // 32-key tiles a wave holds at once
 constexpr int SCORE_WPP = 2 * SCORE_KT;    // pages per wave iteration
 constexpr int NREF_MAX = 256;
@@ -163,13 +162,16 @@ __host__ __device__ constexpr int qb_eff(int qb) {
 }
 __host__ __device__ constexpr int score_rpad(int R) { return 32 * qb_eff((R + 31) / 32); }
 
-// Pages per workgroup (a chunk) of a launch over n_heads rows of max_pages pages.  A chunk
-// pays for its query block, page ids and first tiles before it computes.  A launch whose
-// workgroups share a CU two by two (the bf16 passes) takes the longest chunks that still give
-// it SCORE_TARGET_WG workgroups, one per CU: both passes and the merge, chunks of 128 pages ->
-// this rule: 8 heads x 512 pages 61 -> 26 us (16 pages), 8 x 2048 63 -> 46 (64; 32 pages 53,
-// 16 pages 78), 200 x 128 at G 7 88 -> 81 (64), 32 x 1024 stays at 128 (70; 64 pages 71, 32
-// pages 91).  Never more than SCORE_MAX_PARTS workgroups by shorter chunks (workspace).
+// Pages per workgroup (a chunk) of a pass over n_heads rows of max_pages pages.  Pass 1 always
+// takes SCORE_PPW: its chunks' sums of exponentials are rounded, so other chunks would change a
+// row's LSE in the last bit, and now and then a slot at the Top-p threshold with it, with the
+// number of heads in the call.  Pass 2 and the row probabilities compute every key by itself, the
+// same bits in any chunk.  There a chunk pays for its query block, page ids and first tiles
+// before it computes.  A launch whose workgroups share a CU two by two (the bf16 passes) takes
+// the longest chunks that still give it SCORE_TARGET_WG workgroups, one per CU.  Pass 2, chunks
+// of 128 pages -> this rule: 8 heads x 512 pages 29 -> 11 us (16 pages), 8 x 2048 31 -> 21 (64; 32
+// pages 24, 16 pages 35), 200 x 128 at G 7 43 -> 39 (64; 32 pages 44), 32 x 1024 stays at 128 (33;
+// 64 pages 35, 32 pages 44).
 static int score_ppw(int n_heads, int max_pages) {
   int p = SCORE_PPW;
   while (p > SCORE_PPW_MIN && (long long)n_heads * ((max_pages + p - 1) / p) < SCORE_TARGET_WG) p >>= 1;
@@ -177,12 +179,12 @@ static int score_ppw(int n_heads, int max_pages) {
 }
 // The same where one workgroup fills a CU (fp32, and the redundancy pass): the launch then
 // runs in rounds of one workgroup per CU, each as long as a chunk and its set-up (in pages'
-// time), so 200 workgroups beat 400 half as long.  fp32: 2 heads x 128 pages 150 -> 30 us (16
-// pages), 64 x 256 296 -> 164 (64), 160 x 128 295 -> 279 (32), 200 x 128 stays at 128 (296; 64
-// pages 302).  Redundancy pass (set-up 48: it stages every reference row; whole score call,
-// 512 pages -> this rule): 8 heads x 1024 pages 194 -> 41 us, 32 x 1024 211 -> 98, 64 x 1024
-// 235 -> 176.  Two cases keep the longest chunks, because the rows' lengths differ and then the
-// last round is shorter than counted while every set-up still adds up: a launch that gives
+// time), so 200 workgroups beat 400 half as long.  fp32 pass 2: 2 heads x 128 pages 42 -> 8.5 us
+// (16 pages), 64 x 256 85 -> 49 (64), 160 x 128 85 -> 71 (32), 200 x 128 stays at 128 (88; 64
+// pages 86, 32 pages 91).  Redundancy pass (set-up 48: it stages every reference row; whole
+// score call, 512 pages -> this rule): 8 heads x 1024 pages 194 -> 41 us, 32 x 1024 211 -> 98, 64 x
+// 1024 235 -> 176.  Two cases keep the longest chunks, because the rows' lengths differ and then
+// the last round is shorter than counted while every set-up still adds up: a launch that gives
 // every CU a workgroup with them (552 heads of 295 to 470 pages with redundancy: 506 us, with
 // 256 pages 550), and one that would win less than a tenth (140 heads of 100 to 500 pages: 283
 // us, with 128 pages 291).
@@ -193,7 +195,7 @@ static int score_ppw_rounds(int n_heads, int max_pages, int most, int least, int
   };
   int best = most;
   if (wgs(most) >= SCORE_TARGET_WG) return best;
-  for (int p = most >> 1; p >= least && wgs(p) <= SCORE_MAX_PARTS; p >>= 1)
+  for (int p = most >> 1; p >= least; p >>= 1)
     if (cost(p) < cost(best) && 10 * cost(p) <= 9 * cost(most)) best = p;
   return best;
 }
@@ -510,7 +512,7 @@ template <typename T, int D, int QB>
 __global__ __launch_bounds__(SCORE_NT) void score_pass1_kernel(
     const T* __restrict__ q_obs, const T* __restrict__ k_pool, const int32_t* __restrict__ table,
     const uint16_t* __restrict__ masks, const int32_t* __restrict__ n_pages_arr, int NS, int Hq,
-    int Hkv, int W, int max_pages, float c2, float2* __restrict__ part, int n_chunks, int ppw) {
+    int Hkv, int W, int max_pages, float c2, float2* __restrict__ part, int n_chunks) {
   using F = Frag<T, D>;
   constexpr int R_pad = 32 * QB;
   extern __shared__ __align__(16) char smem[];
@@ -527,7 +529,7 @@ __global__ __launch_bounds__(SCORE_NT) void score_pass1_kernel(
   __syncthreads();
 
   const int n = n_pages_arr[h];
-  const int p_begin = chunk * ppw, p_end = min(p_begin + ppw, n);
+  const int p_begin = chunk * SCORE_PPW, p_end = min(p_begin + SCORE_PPW, n);
   float M[QB], L[QB];
 #pragma unroll
   for (int q = 0; q < QB; ++q) { M[q] = -INFINITY; L[q] = 0.f; }
@@ -963,7 +965,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void score_pass1_coop_kernel(const uint16_t* __restrict__ q_obs, const uint16_t* __restrict__ k_pool,
                              const int32_t* __restrict__ table, const uint16_t* __restrict__ masks,
                              const int32_t* __restrict__ n_pages_arr, int NS, int Hq, int Hkv, int W,
-                             int max_pages, float c2, float2* __restrict__ part, int n_chunks, int ppw) {
+                             int max_pages, float c2, float2* __restrict__ part, int n_chunks) {
   using C = Coop<D, QB>;
   using L = CoopLds<D, QB>;
   constexpr int R_pad = 32 * QB;
@@ -974,9 +976,9 @@ void score_pass1_coop_kernel(const uint16_t* __restrict__ q_obs, const uint16_t*
   const bool active = wave < C::ACTIVE;
   const int ts = wave / QB, qb = wave % QB;
   const int n = n_pages_arr[h];
-  const int p_begin = chunk * ppw, p_end = min(p_begin + ppw, n);
+  const int p_begin = chunk * C::PPW, p_end = min(p_begin + C::PPW, n);
   bf16x8 qf[C::KS];
-  coop_setup<D, QB>(smem, table + (size_t)h * max_pages, masks + (size_t)h * max_pages, p_begin, p_end, ppw,
+  coop_setup<D, QB>(smem, table + (size_t)h * max_pages, masks + (size_t)h * max_pages, p_begin, p_end, C::PPW,
                     q_obs, NS, Hq, Hkv, W, s, kv, qb, active, qf);
   const int32_t* s_table = reinterpret_cast<const int32_t*>(smem + L::TABLE);
   const uint32_t* s_mask = reinterpret_cast<const uint32_t*>(smem + L::MASK);
@@ -1426,27 +1428,13 @@ hipError_t launch_score_rows_t(int NS, int Hq, int Hkv, int W, const void* q_obs
   }
 }
 
-// Workspace bytes for this many chunks per head: the chunks' (max, sum) of every row, then
-// the row LSEs (when the caller takes none).
-static size_t score_ws(long long n_heads, long long n_chunks, int R_pad, long long n_lse) {
-  const size_t part = ((size_t)(n_heads * n_chunks) * R_pad * sizeof(float2) + 255) & ~(size_t)255;
-  return part + (((size_t)n_lse * sizeof(float) + 255) & ~(size_t)255);
-}
-
 template <typename T, int D, int QB>
 hipError_t launch_score_q(const hk_score_args& a, hipStream_t st) {
   const hk_paged_kv* kv = a.kv;
   constexpr int R_pad = 32 * QB;
   const int n_heads = a.NS * a.Hkv;
-  // pass 1 leaves one partial per (head, chunk, row) in the workspace: a workspace that only
-  // holds those of SCORE_PPW-page chunks gets such chunks.  So does a call with the redundancy
-  // metric: other chunks round the row LSEs otherwise in the last bit, and beside the
-  // temperature that is solved from these scores that moved a slot across the Top-p threshold
-  // in 6 of 100 calls of few heads (1.5 of 100 without that metric).
-  const int ppw2 = score_ppw_t<T>(n_heads, kv->max_pages);
-  const int ppw = a.row_lse_in || (!a.x_red && a.ws_bytes >= score_ws(n_heads, (kv->max_pages + ppw2 - 1) / ppw2, R_pad, a.W * a.NS * a.Hq))
-                      ? ppw2 : SCORE_PPW;
-  const int n_chunks = (kv->max_pages + ppw - 1) / ppw;
+  const int n_chunks = (kv->max_pages + SCORE_PPW - 1) / SCORE_PPW;      // of pass 1
+  const int ppw = score_ppw_t<T>(n_heads, kv->max_pages);                // of pass 2
   const float c2 = a.sm_scale * kLog2e;
   char* ws = static_cast<char*>(a.ws);
   float2* part = reinterpret_cast<float2*>(ws);
@@ -1454,7 +1442,7 @@ hipError_t launch_score_q(const hk_score_args& a, hipStream_t st) {
   const size_t off = ((size_t)n_heads * n_chunks * R_pad * sizeof(float2) + 255) & ~(size_t)255;
   if (!lse_buf) lse_buf = reinterpret_cast<float*>(ws + off);
   const float* lse_use = a.row_lse_in;
-  const dim3 grid(n_chunks, n_heads), grid2((kv->max_pages + ppw2 - 1) / ppw2, n_heads);
+  const dim3 grid(n_chunks, n_heads), grid2((kv->max_pages + ppw - 1) / ppw, n_heads);
   // bf16 caches: the cooperative passes; fp32 caches (and the redundancy variant of pass 2):
   // the per-wave tile passes
   constexpr bool coop = sizeof(T) == 2;
@@ -1468,7 +1456,7 @@ hipError_t launch_score_q(const hk_score_args& a, hipStream_t st) {
         hipLaunchKernelGGL((score_pass1_coop_kernel<D, QB>), grid, dim3(Cp::NT), lds, st,
                            static_cast<const uint16_t*>(a.q_obs), static_cast<const uint16_t*>(kv->k_pool),
                            kv->page_table, kv->page_mask, kv->n_pages, a.NS, a.Hq, a.Hkv, a.W,
-                           kv->max_pages, c2, part, n_chunks, ppw);
+                           kv->max_pages, c2, part, n_chunks);
       }
       {
         TimedLaunch t(HK_TK_SCORE_MERGE, st);
@@ -1486,7 +1474,7 @@ hipError_t launch_score_q(const hk_score_args& a, hipStream_t st) {
         hipLaunchKernelGGL((score_pass1_kernel<T, D, QB>), grid, dim3(SCORE_NT), lds1, st,
                            static_cast<const T*>(a.q_obs), static_cast<const T*>(kv->k_pool),
                            kv->page_table, kv->page_mask, kv->n_pages, a.NS, a.Hq, a.Hkv, a.W,
-                           kv->max_pages, c2, part, n_chunks, ppw);
+                           kv->max_pages, c2, part, n_chunks);
       }
       {
         TimedLaunch t(HK_TK_SCORE_MERGE, st);
@@ -1520,14 +1508,14 @@ hipError_t launch_score_q(const hk_score_args& a, hipStream_t st) {
     hipLaunchKernelGGL((score_pass2_coop_kernel<D, QB>), grid2, dim3(Cp::NT), lds, st, static_cast<const uint16_t*>(a.q_obs),
                        static_cast<const uint16_t*>(kv->k_pool), kv->page_table, kv->page_mask,
                        kv->n_pages, a.NS, a.Hq, a.Hkv, a.W, kv->max_pages, a.L_dense, c2, lnR, lse_use,
-                       a.s_attn, a.cand_len, ppw2);
+                       a.s_attn, a.cand_len, ppw);
   } else {
     allow_dynamic_lds<score_pass2_kernel<T, D, QB, false>>(lds2);
     hipLaunchKernelGGL((score_pass2_kernel<T, D, QB, false>), grid2, dim3(P2Shape<false>::NT), lds2, st,
                        static_cast<const T*>(a.q_obs), static_cast<const T*>(kv->k_pool),
                        kv->page_table, kv->page_mask, kv->n_pages, a.NS, a.Hq, a.Hkv, a.W,
                        kv->max_pages, a.L_dense, c2, lnR, lse_use, a.s_attn, a.cand_len,
-                       nullptr, 0, nullptr, ppw2);
+                       nullptr, 0, nullptr, ppw);
   }
   return hipGetLastError();
 }
@@ -1545,20 +1533,12 @@ hipError_t launch_score_t(const hk_score_args& a, hipStream_t st) {
 
 }  // namespace hk
 
-size_t hk_score_ws_min(int NS, int Hq, int Hkv, int W, int max_pages) {
-  return hk::score_ws(NS * Hkv, (max_pages + hk::SCORE_PPW - 1) / hk::SCORE_PPW,
-                      hk::score_rpad(Hq / Hkv * W), W * NS * Hq);
-}
-
-// Few heads take shorter chunks, so more partials than hk_score_ws_min counts: at most
-// SCORE_MAX_PARTS in all, of at least SCORE_PPW_MIN pages each.  Counting that bound instead
-// of the chunks of this very size, on top of the SCORE_PPW-page ones, keeps the bytes
-// growing with the heads and with the table width.
 size_t hk_score_ws(int NS, int Hq, int Hkv, int W, int max_pages) {
-  const long long H = (long long)NS * Hkv, most = H * ((max_pages + hk::SCORE_PPW_MIN - 1) / hk::SCORE_PPW_MIN);
-  const long long parts = H * ((max_pages + hk::SCORE_PPW - 1) / hk::SCORE_PPW) +
-                          std::min(most, (long long)hk::SCORE_MAX_PARTS);
-  return hk::score_ws(parts, 1, hk::score_rpad(Hq / Hkv * W), (long long)W * NS * Hq);
+  const int R_pad = hk::score_rpad(Hq / Hkv * W);
+  const int n_chunks = (max_pages + hk::SCORE_PPW - 1) / hk::SCORE_PPW;
+  const size_t part = ((size_t)NS * Hkv * n_chunks * R_pad * sizeof(float2) + 255) & ~(size_t)255;
+  const size_t lse = ((size_t)W * NS * Hq * sizeof(float) + 255) & ~(size_t)255;
+  return part + lse;
 }
 
 size_t hk_score_lds_bytes(int R, int D, int esize, bool redundancy) {

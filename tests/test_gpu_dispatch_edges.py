@@ -53,36 +53,28 @@ def test_decode_merge_shapes(D, G, dtype, pages):
     _decode_against_oracle(cfg, [pages * 16, 0, pages * 8 + 5], pages, n_split=-(-pages // 16))
 
 
-# chunks of 16 pages up to 128: few rows take short ones; rows that end before, at and past a
-# chunk's edge, or hold nothing.  The least workspace the call accepts holds the partials of
-# 128-page chunks only and gets those.
+# the second pass's chunks of 16 pages up to 128: few rows take short ones; rows that end before,
+# at and past a chunk's edge, or hold nothing.  A workspace below the size asked for is refused.
 @pytest.mark.parametrize("D,G,dtype,pages,lens", [
     (64, 4, "f32", 130, [2080, 256, 257, 0]), (128, 4, "bf16", 130, [2080, 255, 16, 1]),
     (128, 7, "bf16", 40, [640, 512, 513, 300]), (64, 8, "bf16", 66, [1056, 1, 1024, 1025])])
-@pytest.mark.parametrize("least", [False, True])
-def test_score_chunk_lengths(D, G, dtype, pages, lens, least):
+def test_score_chunk_lengths(D, G, dtype, pages, lens):
     import paper_2606_28831_amd as hk
     W, NS, Hkv = 16, 2, 2
     cfg = dict(L=1, B=NS, Hq=Hkv * G, Hkv=Hkv, D=D, N=pages * 16, dtype=dtype, W=W, seed=43, recipe="normal")
     w = WL.make_workload(cfg, DEV, hole_prob=0.1, head_lens=lens, max_pages=pages)
     kv = hk.PagedKV(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
     d = hk.dims(NS, Hkv * G, Hkv, D, W)
-    H, R = NS * Hkv, G * W
-    blocks = next(b for b in (1, 2, 4, 7, 8) if 32 * b >= R)
-    small = -(-H * -(-pages // 128) * 32 * blocks * 8 // 256) * 256 + -(-W * NS * Hkv * G * 4 // 256) * 256
+    H = NS * Hkv
     ws = hk.workspace(hk.OP_SCORE, d, w.max_pages, DEV)
-    assert ws.numel() > small
-    if least:
-        ws = ws[:small]
     ws.fill_(255)
     s = torch.full((H, w.S_max), 7.0, device=DEV)
     cl = torch.empty(H, dtype=torch.int32, device=DEV)
     lse = torch.empty(W, NS, Hkv * G, device=DEV)
     scale = 1 / math.sqrt(D)
     hk.hk_score(d, w.q_obs, kv, 48, scale, s, cl, row_lse_out=lse, ws=ws)
-    if least:
-        with pytest.raises(hk.HardKVError):
-            hk.hk_score(d, w.q_obs, kv, 48, scale, s, cl, row_lse_out=lse, ws=ws[:small - 256])
+    with pytest.raises(hk.HardKVError):
+        hk.hk_score(d, w.q_obs, kv, 48, scale, s, cl, row_lse_out=lse, ws=ws[:ws.numel() - 256])
     torch.cuda.synchronize()
     host = HostCache(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
     qn, sn, ln, rtol = np64(w.q_obs), np64(s), np64(lse), RTOL[dtype]
@@ -308,9 +300,45 @@ def test_decode_bf16_infinite_values_last_page(D, G, n_pages):
         check_lse(np64(lse[h]), ref_l, RTOL["bf16"], f"lse head {h}")
 
 
-# A call with the redundancy metric keeps 128-page chunks in pass 1 (its row LSEs, and with them
-# the log scores, are those of the least workspace bit for bit), while its second pass takes
-# shorter chunks with few heads (2 x 2) and 512-page ones where every CU has a workgroup (64 x 4).
+# A head's row LSEs, log scores and redundancy are the same bits whoever shares its launch (few
+# heads take shorter chunks in the second pass) and however much workspace there is, its row LSEs
+# also whether or not the redundancy is asked for.
+@pytest.mark.parametrize("D,G,dtype,pages", [(128, 4, "bf16", 520), (64, 7, "bf16", 300), (64, 2, "f32", 160)])
+def test_score_of_a_head_does_not_depend_on_the_batch(D, G, dtype, pages):
+    import paper_2606_28831_amd as hk
+    W, NS, Hkv, n_ref = 8, 26, 2, 33
+    lens = [pages * 16 - 37 * (i % 11) for i in range(NS * Hkv)]
+    cfg = dict(L=1, B=NS, Hq=Hkv * G, Hkv=Hkv, D=D, N=pages * 16, dtype=dtype, W=W, seed=67, recipe="normal")
+    w = WL.make_workload(cfg, DEV, head_lens=lens, max_pages=pages)
+    ref = (torch.arange(n_ref, device=DEV, dtype=torch.int32) * (min(lens) // n_ref)).expand(NS * Hkv, n_ref)
+
+    def score(seqs, red, more_ws=0):
+        n, H = len(seqs), len(seqs) * Hkv
+        rows = slice(seqs[0] * Hkv, (seqs[-1] + 1) * Hkv)
+        kv = hk.PagedKV(w.k_pool, w.v_pool, w.page_table[rows].clone(), w.page_mask[rows].clone(),
+                        w.n_pages[rows].clone())
+        d = hk.dims(n, Hkv * G, Hkv, D, W)
+        ws = hk.workspace(hk.OP_SCORE, d, w.max_pages, DEV)
+        ws = torch.full((ws.numel() + more_ws,), 255, dtype=torch.uint8, device=DEV)
+        s, x = (torch.full((H, w.S_max), 7.0, device=DEV) for _ in "sx")
+        cl, lse = torch.empty(H, dtype=torch.int32, device=DEV), torch.empty(W, n, Hkv * G, device=DEV)
+        more = dict(ref_slots=ref[rows].contiguous(), n_ref=n_ref, x_red=x) if red else {}
+        hk.hk_score(d, w.q_obs[:, seqs[0]:seqs[-1] + 1].contiguous(), kv, 48, 1 / math.sqrt(D), s, cl,
+                    row_lse_out=lse, ws=ws, **more)
+        torch.cuda.synchronize()
+        return s, lse, x
+
+    all_of = {red: score(range(NS), red) for red in (False, True)}
+    for seqs in (range(NS), range(3), range(17, 18)):
+        rows, at = slice(seqs[0] * Hkv, (seqs[-1] + 1) * Hkv), slice(seqs[0], seqs[-1] + 1)
+        for red, more_ws in ((True, 0), (False, 0), (False, 1 << 24)):
+            s, lse, x = score(seqs, red, more_ws)
+            assert all(torch.equal(lse, a[1][:, at]) for a in all_of.values()), (list(seqs), red, more_ws)
+            assert torch.equal(s, all_of[red][0][rows]) and torch.equal(x, all_of[red][2][rows])
+
+
+# The redundancy pass takes shorter chunks with few heads (2 x 2) and 512-page ones where every CU
+# has a workgroup (64 x 4).
 @pytest.mark.parametrize("NS,Hkv,pages", [(2, 2, 520), (64, 4, 34)])
 def test_redundancy_chunk_lengths(NS, Hkv, pages):
     import paper_2606_28831_amd as hk
@@ -321,19 +349,13 @@ def test_redundancy_chunk_lengths(NS, Hkv, pages):
     w = WL.make_workload(cfg, DEV, head_lens=lens, max_pages=pages)
     kv = hk.PagedKV(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
     d = hk.dims(NS, Hkv * G, Hkv, D, W)
-    full = hk.workspace(hk.OP_SCORE, d, w.max_pages, DEV)
-    small = -(-H * -(-w.max_pages // 128) * 32 * 8 // 256) * 256 + -(-W * NS * Hkv * G * 4 // 256) * 256
     ref = (torch.arange(n_ref, device=DEV, dtype=torch.int32) * (least // n_ref)).expand(H, n_ref).contiguous()
-    out = []
-    for ws in (full, full[:small]):
-        s, x = (torch.full((H, w.S_max), 7.0, device=DEV) for _ in "sx")
-        cl, lse = torch.empty(H, dtype=torch.int32, device=DEV), torch.empty(W, NS, Hkv * G, device=DEV)
-        hk.hk_score(d, w.q_obs, kv, 48, 1 / math.sqrt(D), s, cl, row_lse_out=lse, ref_slots=ref, n_ref=n_ref, x_red=x,
-                    ws=ws)
-        out.append((s, lse, x))
-    for a, b in zip(*out):
-        assert torch.equal(a, b)
-    x = np64(out[0][2])
+    s, x = (torch.full((H, w.S_max), 7.0, device=DEV) for _ in "sx")
+    cl, lse = torch.empty(H, dtype=torch.int32, device=DEV), torch.empty(W, NS, Hkv * G, device=DEV)
+    hk.hk_score(d, w.q_obs, kv, 48, 1 / math.sqrt(D), s, cl, row_lse_out=lse, ref_slots=ref, n_ref=n_ref, x_red=x,
+                ws=hk.workspace(hk.OP_SCORE, d, w.max_pages, DEV))
+    torch.cuda.synchronize()
+    x = np64(x)
     host = HostCache(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
     for h in (0, H - 1):
         K, valid = host.head(h)
