@@ -171,10 +171,14 @@ __host__ __device__ constexpr int score_rpad(int R) { return 32 * qb_eff((R + 31
 // the longest chunks that still give it SCORE_TARGET_WG workgroups, one per CU.  Pass 2, chunks
 // of 128 pages -> this rule: 8 heads x 512 pages 29 -> 11 us (16 pages), 8 x 2048 31 -> 21 (64; 32
 // pages 24, 16 pages 35), 200 x 128 at G 7 43 -> 39 (64; 32 pages 44), 32 x 1024 stays at 128 (33;
-// 64 pages 35, 32 pages 44).
-static int score_ppw(int n_heads, int max_pages) {
+// 64 pages 35, 32 pages 44).  `one_per_cu`: never more than SCORE_TARGET_WG workgroups by shorter
+// chunks, where two of them on a CU are no faster than one twice as long: four query blocks at D
+// 128 keep all eight waves in MFMAs (G 4, W 32: 224 x 128 stays at 128: 31.4 us, 64 pages 32.7; 96 x
+// 128 takes 64: 21, 32 pages 23; at G 2, G 7 or D 64 the second workgroup is worth 10 to 20%).
+static int score_ppw(int n_heads, int max_pages, bool one_per_cu) {
+  const auto wgs = [&](int p) { return (long long)n_heads * ((max_pages + p - 1) / p); };
   int p = SCORE_PPW;
-  while (p > SCORE_PPW_MIN && (long long)n_heads * ((max_pages + p - 1) / p) < SCORE_TARGET_WG) p >>= 1;
+  while (p > SCORE_PPW_MIN && wgs(p) < SCORE_TARGET_WG && !(one_per_cu && wgs(p >> 1) > SCORE_TARGET_WG)) p >>= 1;
   return p;
 }
 // The same where one workgroup fills a CU (fp32, and the redundancy pass): the launch then
@@ -199,10 +203,21 @@ static int score_ppw_rounds(int n_heads, int max_pages, int most, int least, int
     if (cost(p) < cost(best) && 10 * cost(p) <= 9 * cost(most)) best = p;
   return best;
 }
+// Pages per workgroup of pass 2 (without redundancy) and of the row probabilities.  The latter
+// write R rows per head: from 128 workgroups on the writes bound them and 64-page chunks only
+// add workgroups (bf16, W 32: 160 heads x 128 pages at G 4 42 us, with 64 pages 53; 32 x 512 at G
+// 7 65 and 70; 8 x 2048 at G 4 40.7 and 41.7); with fewer the chunks shorten as in pass 2 (8 x 512
+// at G 4 35 -> 11 us).
+template <typename T, int D, int QB>
+static int score_ppw2(int n_heads, int max_pages) {
+  if (sizeof(T) == 4) return score_ppw_rounds(n_heads, max_pages, SCORE_PPW, SCORE_PPW_MIN, 8);
+  return score_ppw(n_heads, max_pages, D == 128 && QB == 4);
+}
 template <typename T>
-static int score_ppw_t(int n_heads, int max_pages) {
-  return sizeof(T) == 2 ? score_ppw(n_heads, max_pages)
-                        : score_ppw_rounds(n_heads, max_pages, SCORE_PPW, SCORE_PPW_MIN, 8);
+static int score_ppw_rows(int n_heads, int max_pages) {
+  if (sizeof(T) == 4) return score_ppw_rounds(n_heads, max_pages, SCORE_PPW, SCORE_PPW_MIN, 8);
+  if ((long long)n_heads * ((max_pages + SCORE_PPW - 1) / SCORE_PPW) >= SCORE_TARGET_WG / 2) return SCORE_PPW;
+  return score_ppw(n_heads, max_pages, false);
 }
 
 // MFMA chain of one 32x32 output block over the whole head dimension.  LDS_IS_A: the
@@ -1404,7 +1419,7 @@ hipError_t launch_score_rows_q(int NS, int Hq, int Hkv, int W, const void* q_obs
                                const float* row_lse, float* a_rows, hipStream_t st) {
   constexpr int R_pad = 32 * QB;
   const int n_heads = NS * Hkv;
-  const int ppw = score_ppw_t<T>(n_heads, kv->max_pages), n_chunks = (kv->max_pages + ppw - 1) / ppw;
+  const int ppw = score_ppw_rows<T>(n_heads, kv->max_pages), n_chunks = (kv->max_pages + ppw - 1) / ppw;
   const size_t lds = (size_t)R_pad * D * sizeof(T) + (size_t)R_pad * sizeof(float);
   allow_dynamic_lds<score_rows_kernel<T, D, QB>>(lds);
   TimedLaunch t(HK_TK_SCORE_ROWS, st);
@@ -1434,7 +1449,7 @@ hipError_t launch_score_q(const hk_score_args& a, hipStream_t st) {
   constexpr int R_pad = 32 * QB;
   const int n_heads = a.NS * a.Hkv;
   const int n_chunks = (kv->max_pages + SCORE_PPW - 1) / SCORE_PPW;      // of pass 1
-  const int ppw = score_ppw_t<T>(n_heads, kv->max_pages);                // of pass 2
+  const int ppw = score_ppw2<T, D, QB>(n_heads, kv->max_pages);         // of pass 2
   const float c2 = a.sm_scale * kLog2e;
   char* ws = static_cast<char*>(a.ws);
   float2* part = reinterpret_cast<float2*>(ws);
