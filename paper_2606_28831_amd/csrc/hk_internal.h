@@ -4,9 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <atomic>
-
 #include "hardkv.h"
+#include "hk_lds_limit.h"
 
 #define HK_PAGE 16
 #define HK_WAVE 64
@@ -152,13 +151,11 @@ __device__ __forceinline__ int dense_pages(int L_dense) { return (L_dense + HK_P
 // caller records into a graph) make no further API calls.
 template <auto Kernel>
 inline void allow_dynamic_lds(size_t bytes) {
-  static std::atomic<size_t> granted{65536};
-  size_t g = granted.load(std::memory_order_relaxed);
-  if (bytes <= g) return;
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  while (g < bytes && !granted.compare_exchange_weak(g, bytes)) {
-  }
+  static LdsLimit limit(65536);
+  limit.raise(bytes, [](size_t b) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)b);
+  });
 }
 
 // Records HIP events around one kernel launch on its stream while kernel timing is on

@@ -860,13 +860,14 @@ hipError_t hk_launch_select_wide(int n_heads, int S_max, const int32_t* cand_len
   // the finishing workgroup's list never holds more keys than the row has slots: rows of up to
   // SW_SHORT slots leave LDS for a second workgroup on the CU
   const int list_cap = std::min(std::max((S_max + 63) & ~63, SW_LIST_MIN), SW_LIST);
-  const size_t lds = (size_t)list_cap * 4 + SW_B2 * 12;
+  const auto lds_of = [](int cap) { return (size_t)cap * 4 + SW_B2 * 12; };
+  const size_t lds = lds_of(list_cap);
   if (S_max <= SW_SHORT && n_heads > 256) {
-    allow_dynamic_lds<sw_finish_kernel<SW_FS>>(lds);
+    allow_dynamic_lds<sw_finish_kernel<SW_FS>>(lds_of(SW_SHORT));     // raised once: the most it takes
     hipLaunchKernelGGL(sw_finish_kernel<SW_FS>, dim3(n_heads), dim3(SW_FS), lds, st, S_max, C, skip, cand_len,
                        list_cap, hp, ho, sorted, p_q, k_min, k_max, params, k_out, sel_mass);
   } else {
-    allow_dynamic_lds<sw_finish_kernel<SW_FT>>(lds);
+    allow_dynamic_lds<sw_finish_kernel<SW_FT>>(lds_of(SW_LIST));
     hipLaunchKernelGGL(sw_finish_kernel<SW_FT>, dim3(n_heads), dim3(SW_FT), lds, st, S_max, C, skip, cand_len,
                        list_cap, hp, ho, sorted, p_q, k_min, k_max, params, k_out, sel_mass);
   }
