@@ -986,7 +986,9 @@ __global__ __launch_bounds__(BP_NT) void budget_plan_kernel(int max_pages,
 // ------------------------------------------------------------------ budget selection
 // RANK_C: keys are (votes, c); else the votes alone, in 32 bits, whose search is one round.
 // All of a thread's votes are loaded before any is used (behind the tests of an element each
-// load was waited on by itself).
+// load was waited on by itself), but for 64-bit keys in 512 threads, which gain nothing (8 heads
+// x 4128 slots with c 16.1 us, with them 16.7), and 64 of them, which spill already and would
+// spill more (8 x 65536 123 us, with them 163).
 template <int NT, int EPT, bool RANK_C>
 __global__ __launch_bounds__(NT) void budget_select_kernel(
     int S_max, const int32_t* __restrict__ cand_len, const uint16_t* __restrict__ mask,
@@ -1000,8 +1002,10 @@ __global__ __launch_bounds__(NT) void budget_select_kernel(
   const float* crow = c ? c + (size_t)h * S_max : nullptr;
   const uint32_t* srow = sel_in ? sel_in + (size_t)h * (S_max / 32) : nullptr;
   K key[EPT];                        // rank keys of the base set, all ones elsewhere
+  constexpr bool UP_FRONT = !RANK_C || (NT == 1024 && EPT < 64);
+  if constexpr (UP_FRONT)
 #pragma unroll
-  for (int i = 0; i < EPT; ++i) key[i] = vrow ? (K)vrow[min(tid + NT * i, S_max - 1)] : K(1);
+    for (int i = 0; i < EPT; ++i) key[i] = vrow ? (K)vrow[min(tid + NT * i, S_max - 1)] : K(1);
   const uint64_t cf = cand_flags<EPT>(h, S_max, cand_len, mask, sh);
   const int mode = head_mode ? head_mode[h] : HK_BUDGET_REWRITE;
   uint32_t* brow = sel_out + (size_t)h * (S_max / 32);
@@ -1018,13 +1022,16 @@ __global__ __launch_bounds__(NT) void budget_select_kernel(
 #pragma unroll
   for (int i = 0; i < EPT; ++i) {
     const int j = tid + NT * i;
-    const uint32_t vt = (uint32_t)key[i];
+    uint32_t vt = 1u;
+    if constexpr (UP_FRONT) vt = (uint32_t)key[i];
     key[i] = ~K(0);
     if (!((cf >> i) & 1ull)) continue;
     if (j < n_sink) {
       sinks |= 1ull << i;
       continue;
     }
+    if constexpr (!UP_FRONT)
+      if (vrow) vt = vrow[j];
     if (vt == 0u) continue;
     if (srow && !((srow[j >> 5] >> (j & 31)) & 1u)) continue;
     K k;
@@ -1110,22 +1117,40 @@ struct VoteLaunch {
   }
 };
 
-template <int NT, int EPT>
-struct BudgetSelectLaunch {
-  static hipError_t run(int n_heads, int S_max, const int32_t* cand_len, const uint16_t* mask,
-                        const uint16_t* votes, const float* c, const uint32_t* sel_in,
-                        const int32_t* head_mode, const int32_t* k_cap, int n_sink, uint32_t* sel_out,
-                        int32_t* k_out, hipStream_t st) {
-    TimedLaunch t(HK_TK_BUDGET_SELECT, st);
-    if (c)
-      hipLaunchKernelGGL((budget_select_kernel<NT, EPT, true>), dim3(n_heads), dim3(NT), 0, st, S_max,
-                         cand_len, mask, votes, c, sel_in, head_mode, k_cap, n_sink, sel_out, k_out);
-    else
-      hipLaunchKernelGGL((budget_select_kernel<NT, EPT, false>), dim3(n_heads), dim3(NT), 0, st, S_max,
-                         cand_len, mask, votes, c, sel_in, head_mode, k_cap, n_sink, sel_out, k_out);
-    return hipGetLastError();
+template <int NT, int EPT, bool RANK_C>
+static hipError_t run_budget_select(int n_heads, int S_max, const int32_t* cand_len, const uint16_t* mask,
+                                    const uint16_t* votes, const float* c, const uint32_t* sel_in,
+                                    const int32_t* head_mode, const int32_t* k_cap, int n_sink,
+                                    uint32_t* sel_out, int32_t* k_out, hipStream_t st) {
+  TimedLaunch t(HK_TK_BUDGET_SELECT, st);
+  hipLaunchKernelGGL((budget_select_kernel<NT, EPT, RANK_C>), dim3(n_heads), dim3(NT), 0, st, S_max,
+                     cand_len, mask, votes, c, sel_in, head_mode, k_cap, n_sink, sel_out, k_out);
+  return hipGetLastError();
+}
+
+// One workgroup per head and the fewest elements per thread that cover the row; past 4096
+// slots, with c past 8192, 1024 threads, which halve the chain of loads and list steps of 512
+// with twice the elements (128 heads x 32768 slots, no c: 103 us with 512 threads and 64-bit
+// keys, 50 now; 8 x 16384 with c 31 -> 28).  With c they fill a CU with one workgroup, where two
+// of 512 threads fit: 400 heads x 8192 slots 26 us with 512 threads, 40 with 1024.
+template <bool RANK_C, typename... A>
+static hipError_t budget_select_by_size(int n_heads, int S_max, A... a) {
+  if (S_max > (RANK_C ? 8192 : 4096)) {
+    const int e = (S_max + 1023) / 1024;
+    if constexpr (!RANK_C)
+      if (e <= 8) return run_budget_select<1024, 8, RANK_C>(n_heads, S_max, a...);
+    if (e <= 16) return run_budget_select<1024, 16, RANK_C>(n_heads, S_max, a...);
+    if (e <= 32) return run_budget_select<1024, 32, RANK_C>(n_heads, S_max, a...);
+    return run_budget_select<1024, 64, RANK_C>(n_heads, S_max, a...);
   }
-};
+  const int e = (S_max + 511) / 512;
+  if (e <= 1) return run_budget_select<512, 1, RANK_C>(n_heads, S_max, a...);
+  if (e <= 2) return run_budget_select<512, 2, RANK_C>(n_heads, S_max, a...);
+  if (e <= 4) return run_budget_select<512, 4, RANK_C>(n_heads, S_max, a...);
+  if constexpr (RANK_C)
+    if (e > 8) return run_budget_select<512, 16, RANK_C>(n_heads, S_max, a...);
+  return run_budget_select<512, 8, RANK_C>(n_heads, S_max, a...);
+}
 
 }  // namespace hk
 
@@ -1152,22 +1177,8 @@ hipError_t hk_launch_budget_select(int n_heads, int S_max, const int32_t* cand_l
                                    const uint32_t* sel_in, const int32_t* head_mode,
                                    const int32_t* k_cap, int n_sink, uint32_t* sel_out,
                                    int32_t* k_out, hipStream_t st) {
-  // One workgroup per head and the fewest elements per thread that cover the row; past 4096
-  // slots 1024 threads, which halve the chain of loads and list steps of 512 with twice the
-  // elements (128 heads x 32768 slots, no c: 103 us with 512 threads and 64-bit keys, 50 now).
-  const int e = S_max > 4096 ? (S_max + 1023) / 1024 : (S_max + 511) / 512;
-#define HK_SELECT(NT_, E_)                                                                          \
-  return BudgetSelectLaunch<NT_, E_>::run(n_heads, S_max, cand_len, mask, votes, c, sel_in, head_mode, \
-                                          k_cap, n_sink, sel_out, k_out, st)
-  if (S_max > 4096) {
-    if (e <= 8) HK_SELECT(1024, 8);
-    if (e <= 16) HK_SELECT(1024, 16);
-    if (e <= 32) HK_SELECT(1024, 32);
-    HK_SELECT(1024, 64);
-  }
-  if (e <= 1) HK_SELECT(512, 1);
-  if (e <= 2) HK_SELECT(512, 2);
-  if (e <= 4) HK_SELECT(512, 4);
-  HK_SELECT(512, 8);
-#undef HK_SELECT
+  return c ? budget_select_by_size<true>(n_heads, S_max, cand_len, mask, votes, c, sel_in, head_mode, k_cap,
+                                         n_sink, sel_out, k_out, st)
+           : budget_select_by_size<false>(n_heads, S_max, cand_len, mask, votes, c, sel_in, head_mode, k_cap,
+                                          n_sink, sel_out, k_out, st);
 }

@@ -200,7 +200,8 @@ def test_budget_plan(name):
 
 
 # ---------------------------------------------------------------- budget selection
-@pytest.mark.parametrize("S", [64, 2048, 32768, 33792, 65536])
+# both sides of the sizes where a workgroup changes its threads or their elements
+@pytest.mark.parametrize("S", [64, 1024, 2048, 4096, 4128, 8192, 8224, 16384, 16416, 32768, 33792, 65536])
 @pytest.mark.parametrize("use", ["votes_c", "votes_only", "c_sel_in", "all"])
 def test_budget_select(S, use):
     import paper_2606_28831_amd as hk
