@@ -9,8 +9,9 @@
 //   pass 1  per (head, page chunk): C[key][query] = K Q^T on MFMA 32x32, per-lane online
 //           (max, sum exp) for the lane's query column, merged over lanes and waves;
 //   merge   per (head, row): combine chunk partials into LSE_r;
-//   pass 2  per (head, page chunk): C[query][key] = Q K^T on MFMA 32x32, per-lane column
-//           sum of exp(z - LSE) over the window rows; optionally, on the same K fragment,
+//   pass 2  per (head, page chunk; shorter chunks than pass 1 where few heads would leave CUs
+//           idle): C[query][key] = Q K^T on MFMA 32x32, per-lane column sum of exp(z - LSE)
+//           over the window rows; optionally, on the same K fragment,
 //           C[ref][key] = Kref K^T for the cosine-redundancy metric.
 //
 // Operand mapping.  For the 32-row MFMA operands (32x32x16 bf16, 32x32x2 f32) lane l
@@ -185,13 +186,13 @@ static int score_ppw(int n_heads, int max_pages, bool one_per_cu) {
 // runs in rounds of one workgroup per CU, each as long as a chunk and its set-up (in pages'
 // time), so 200 workgroups beat 400 half as long.  fp32 pass 2: 2 heads x 128 pages 42 -> 8.5 us
 // (16 pages), 64 x 256 85 -> 49 (64), 160 x 128 85 -> 71 (32), 200 x 128 stays at 128 (88; 64
-// pages 86, 32 pages 91).  Redundancy pass (set-up 48: it stages every reference row; whole
-// score call, 512 pages -> this rule): 8 heads x 1024 pages 194 -> 41 us, 32 x 1024 211 -> 98, 64 x
-// 1024 235 -> 176.  Two cases keep the longest chunks, because the rows' lengths differ and then
-// the last round is shorter than counted while every set-up still adds up: a launch that gives
-// every CU a workgroup with them (552 heads of 295 to 470 pages with redundancy: 506 us, with
-// 256 pages 550), and one that would win less than a tenth (140 heads of 100 to 500 pages: 283
-// us, with 128 pages 291).
+// pages 86, 32 pages 91).  Redundancy pass (set-up 48: it stages every reference row; 512 pages ->
+// this rule, the pass alone): 8 heads x 1024 pages 178 -> 24 us, 32 x 1024 179 -> 66, 64 x 1024 182
+// -> 123.  Two cases keep the longest chunks, because the rows' lengths differ and then the last
+// round is shorter than counted while every set-up still adds up: a launch that gives every CU
+// a workgroup with them (whole score call of 552 heads of 295 to 470 pages with redundancy: 506
+// us, with 256 pages 550), and one that would win less than a tenth (140 heads of 100 to 500
+// pages: 283 us, with 128 pages 291).
 static int score_ppw_rounds(int n_heads, int max_pages, int most, int least, int setup) {
   const auto wgs = [&](int p) { return (long long)n_heads * ((max_pages + p - 1) / p); };
   const auto cost = [&](int p) {
