@@ -3,17 +3,19 @@
 //
 //   vote_topp    one workgroup per (head, window row): the row's own Top-p
 //                set of the candidates under its attention probabilities (the a3 rule),
-//                written as a per-row bitmap, found by a radix search over the keys;
+//                written as a per-row bitmap, found by a radix search over the mass;
 //   vote_count   votes[h][j] = number of rows whose set holds j (column bit counts);
-//   budget_plan  one wave per head: the head's state from its page count and valid slots
-//                against L_lower / L_upper, and its cap;
+//   budget_plan  one workgroup per head: the head's state from its page count and valid
+//                slots against L_lower / L_upper, and its cap;
 //   budget_select one workgroup per head: sinks, then the base set ranked by (votes, c,
-//                slot) and cut at the cap by a radix search on the 64-bit rank key.
+//                slot) and cut at the cap by a radix search over the rank keys (votes and c
+//                in 64 bits, votes alone in 32).
 //
-// Layout: NT threads per workgroup (512 up to 32768 slots, 1024 up to 65536); slot j of a
-// row is thread j % NT's element j / NT, so a wave's 64 lanes cover 64 consecutive slots
+// Layout of vote_topp and budget_select: NT threads per workgroup; slot j of a row is
+// thread j % NT's element j / NT, so a wave's 64 lanes cover 64 consecutive slots
 // (coalesced loads; one ballot gives two words of a bitmap).  A row's keys stay in
-// registers (at most 64 each).
+// registers (at most 64 each).  The votes take 512 threads up to 32768 slots and 1024 up to
+// 65536; the selection's rule is at its launch.
 #include <type_traits>
 
 #include "hk_internal.h"
@@ -141,19 +143,6 @@ __device__ __forceinline__ void block_key_range(K kmin, K kmax, BgLds<NT>& sh, K
   }
 }
 
-template <int NT>
-__device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* red) {
-  constexpr int BG_NW = NT / 64;
-  v = wave_reduce_u32(v, 0u, [](uint32_t a, uint32_t b) { return a + b; });
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  uint32_t r = 0;
-#pragma unroll
-  for (int i = 0; i < BG_NW; ++i) r += red[i];
-  return r;
-}
-
 // Exclusive prefix (thread order) of one int per thread (.x) and the block sum (.y).
 template <int NT>
 __device__ __forceinline__ int2 block_exscan_bg(int v, int* red) {
@@ -177,14 +166,11 @@ __device__ __forceinline__ int2 block_exscan_bg(int v, int* red) {
   return make_int2(before + x - v, all);
 }
 
-// After a histogram round: the largest digit d with above + W(digits >= d) >= target, and
-// above + W(digits > d).  Thread t owns digits [t * BPT, (t + 1) * BPT); a suffix scan over
+// After a histogram round: the largest digit d with above + N(digits >= d) >= target, and
+// above + N(digits > d).  Thread t owns digits [t * BPT, (t + 1) * BPT); a suffix scan over
 // the threads' sums finds the one thread whose digits hold the crossing.
-// On the first round the target is not known yet: it is target_of(the histogram's total),
-// which is every member's weight; it comes back in *target (0: nothing to reach, no digit).
-template <int NT, typename TF>
-__device__ __forceinline__ void pick_digit(BgLds<NT>& sh, bool first, TF target_of,
-                                           unsigned long long* target_io,
+template <int NT>
+__device__ __forceinline__ void pick_digit(BgLds<NT>& sh, unsigned long long target,
                                            unsigned long long above, uint32_t* d_out,
                                            unsigned long long* above_out) {
   constexpr int BG_NW = NT / 64, BINS_PER_THREAD = RADIX_BINS / NT;
@@ -202,14 +188,6 @@ __device__ __forceinline__ void pick_digit(BgLds<NT>& sh, bool first, TF target_
   __syncthreads();
   unsigned long long suf = x - own;
   for (int w = wave + 1; w < BG_NW; ++w) suf += sh.red64[w];
-  if (first) {
-    unsigned long long total = 0;
-#pragma unroll
-    for (int w = 0; w < BG_NW; ++w) total += sh.red64[w];
-    *target_io = target_of(total);
-  }
-  const unsigned long long target = *target_io;
-  if (target == 0) return;
   const unsigned long long lo_m = above + suf;
   if (lo_m < target && lo_m + own >= target) {
     unsigned long long cum = lo_m;
@@ -261,61 +239,39 @@ __device__ __forceinline__ int stage_list(const K* key, int pos, K prefix, BgLds
   return sc.y;
 }
 
-// Largest key v of the member elements with W(key >= v) >= target, where W sums the
-// elements' weights (weight(key) of each) and target = target_of(W(all members)), which
-// must not exceed W(all members); the target comes back in *target_out, and for a target
-// of 0 nothing else is computed (v is then meaningless).  Member
-// keys have their top bit clear; every other element holds the all-ones key, which the
-// tests below exclude, so no per-element flags are needed.  The
-// bits above the highest one where the flagged keys differ are common to all of them,
-// hence to v; below them v is found RADIX_BITS at a time from a histogram of weights per
-// digit (LDS atomics) and a suffix scan over the digits.  The first round reads the keys
-// in registers; the keys that share the digits found so far are then packed into an LDS
-// list (when they fit) and the remaining rounds read only that list.  Returns v and, in
-// *above, W(key > v).
-template <int EPT, typename K, typename WF, typename TF, int NT>
-__device__ __forceinline__ K radix_threshold(const K* key, TF target_of, WF weight, K kmin, K kmax,
-                                             BgLds<NT>& sh, unsigned long long* target_out,
-                                             unsigned long long* above_out) {
-  constexpr int CAP = BG_LIST_BYTES / (int)sizeof(K);
+// Largest key v of the member elements such that at least `target` of them have key >= v (1 <=
+// target <= their number); *above is the number with key > v.  Every other element holds the
+// all-ones key, which no member has and the tests below exclude, so no per-element flags are
+// needed.  The bits above the highest one where the members' keys differ are common to all
+// of them, hence to v; below them v is found RADIX_BITS at a time from a histogram per digit
+// (LDS atomics) and a suffix scan over the digits.  The first round reads the keys in
+// registers; the keys that share the digits found so far are then packed into an LDS list
+// (when they fit) and the remaining rounds read only that list.
+template <int EPT, typename K, int NT>
+__device__ __forceinline__ K radix_threshold(const K* key, unsigned long long target, K kmin, K kmax,
+                                             BgLds<NT>& sh, unsigned long long* above_out) {
   const int tid = threadIdx.x;
   K* list = reinterpret_cast<K*>(sh.list);
   *above_out = 0;
-  if (kmin == kmax) {
-    // one key value: the total is the members' count times its weight
-    int cnt = 0;
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) cnt += (key[i] == kmin) ? 1 : 0;
-    cnt = block_sum_int<NT>(cnt, sh.redi);
-    *target_out = target_of((unsigned long long)cnt * weight(kmin));
-    return kmin;
-  }
-  unsigned long long target = 0;
+  if (kmin == kmax) return kmin;     // one key value
   int pos = highest_bit<K>(kmin ^ kmax) + 1;
   K prefix = kmin & ~low_mask<K>(pos);
   unsigned long long above = 0;
   int n_list = -1;                   // < 0: keys still read from registers
   {
-    // First round, outside the loop (inside it the compiler would keep the EPT weights,
-    // which no later round changes, in registers of their own).  Every member shares the
-    // prefix, so the only test is against the all-ones key of non-members, and a
-    // member's digit is its key minus the prefix, shifted.  (Sending non-members to a
-    // spare bin instead would serialise their atomics on one address.)
+    // First round: every member shares the prefix, so the only test is against the all-ones
+    // key of non-members, and a member's digit is its key minus the prefix, shifted.  (Sending
+    // non-members to a spare bin instead would serialise their atomics on one address.)
     const int nb = min(RADIX_BITS, pos), lo = pos - nb;
     clear_hist(sh);
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
       const K k = key[i];
-      if (k != ~K(0)) atomicAdd(&sh.hist[(uint32_t)((k - prefix) >> lo)], weight(k));
+      if (k != ~K(0)) atomicAdd(&sh.hist[(uint32_t)((k - prefix) >> lo)], 1ull);
     }
     __syncthreads();
     uint32_t d;
-    pick_digit(sh, true, target_of, &target, above, &d, &above);
-    if (target == 0) {
-      *target_out = 0;
-      *above_out = 0;
-      return prefix;
-    }
+    pick_digit(sh, target, above, &d, &above);
     prefix |= (K)d << lo;
     pos = lo;
     if (pos > 0) n_list = stage_list<EPT>(key, pos, prefix, sh);
@@ -328,26 +284,22 @@ __device__ __forceinline__ K radix_threshold(const K* key, TF target_of, WF weig
     if (n_list < 0) {
 #pragma unroll
       for (int i = 0; i < EPT; ++i) {
-        // (an opaque key keeps the compiler from hoisting the EPT weights, which do not
-        // change between rounds, into registers of their own: they would spill)
         const K k = opaque(key[i]);
-        if ((k & hi_mask) == prefix)
-          atomicAdd(&sh.hist[(uint32_t)(k >> lo) & dmask], weight(k));
+        if ((k & hi_mask) == prefix) atomicAdd(&sh.hist[(uint32_t)(k >> lo) & dmask], 1ull);
       }
     } else {
       for (int j = tid; j < n_list; j += NT) {
         const K k = list[j];
-        if ((k & hi_mask) == prefix) atomicAdd(&sh.hist[(uint32_t)(k >> lo) & dmask], weight(k));
+        if ((k & hi_mask) == prefix) atomicAdd(&sh.hist[(uint32_t)(k >> lo) & dmask], 1ull);
       }
     }
     __syncthreads();
     uint32_t d;
-    pick_digit(sh, false, target_of, &target, above, &d, &above);
+    pick_digit(sh, target, above, &d, &above);
     prefix |= (K)d << lo;
     pos = lo;
     if (pos > 0 && n_list < 0) n_list = stage_list<EPT>(key, pos, prefix, sh);
   }
-  *target_out = target;
   *above_out = above;
   return prefix;
 }
@@ -1058,11 +1010,8 @@ __global__ __launch_bounds__(NT) void budget_select_kernel(
     sel |= base;
   } else if (cap > 0) {
     block_key_range<K>(kmin, kmax, sh, &kmin, &kmax);
-    unsigned long long cnt_gt = 0, tgt = 0;
-    const unsigned long long capu = (unsigned long long)cap;
-    const K v = radix_threshold<EPT, K>(
-        key, [capu](unsigned long long) { return capu; }, [](K) { return 1ull; }, kmin, kmax, sh,
-        &tgt, &cnt_gt);
+    unsigned long long cnt_gt = 0;
+    const K v = radix_threshold<EPT, K>(key, (unsigned long long)cap, kmin, kmax, sh, &cnt_gt);
     const int take = cap - (int)cnt_gt;
     uint64_t tie = 0;
     const uint64_t fb = opaque(base);
@@ -1082,40 +1031,38 @@ __global__ __launch_bounds__(NT) void budget_select_kernel(
   if (tid == 0) k_out[h] = n_sinks + cap;
 }
 
-// 512 threads and the fewest elements per thread that cover the row, or, past 512 * 64
-// slots, 1024 threads with 64 elements each
-template <template <int, int> class Launch, typename... A>
-hipError_t by_ept(int S_max, A... args) {
-  if (S_max > BG_SLOTS_512) return Launch<1024, 64>::run(args...);
-  const int e = (S_max + 511) / 512;
-  if (e <= 1) return Launch<512, 1>::run(args...);
-  if (e <= 2) return Launch<512, 2>::run(args...);
-  if (e <= 4) return Launch<512, 4>::run(args...);
-  if (e <= 8) return Launch<512, 8>::run(args...);
-  if (e <= 16) return Launch<512, 16>::run(args...);
-  if (e <= 32) return Launch<512, 32>::run(args...);
-  return Launch<512, 64>::run(args...);
+template <int NT, int EPT>
+static hipError_t run_vote_topp(int S_max, int n_heads, int R, const int32_t* cand_len, const uint16_t* mask,
+                                const float* a_rows, int p_q, uint16_t* votes, int32_t* row_k,
+                                uint32_t* row_sel, int32_t* status, hipStream_t st) {
+  {
+    TimedLaunch t(HK_TK_VOTE, st);
+    hipLaunchKernelGGL((vote_topp_kernel<NT, EPT>), dim3(R, n_heads), dim3(NT), 0, st, R, S_max,
+                       cand_len, mask, a_rows, p_q, row_sel, row_k, status);
+  }
+  {
+    TimedLaunch t(HK_TK_VOTE_COUNT, st);
+    const int nw = S_max / 32;
+    hipLaunchKernelGGL(vote_count_kernel, dim3((nw + VC_NT - 1) / VC_NT, n_heads), dim3(VC_NT), 0,
+                       st, R, S_max, row_sel, votes);
+  }
+  return hipGetLastError();
 }
 
-template <int NT, int EPT>
-struct VoteLaunch {
-  static hipError_t run(int n_heads, int R, int S_max, const int32_t* cand_len, const uint16_t* mask,
-                        const float* a_rows, int p_q, uint32_t* row_sel, int32_t* row_k,
-                        int32_t* status, uint16_t* votes, hipStream_t st) {
-    {
-      TimedLaunch t(HK_TK_VOTE, st);
-      hipLaunchKernelGGL((vote_topp_kernel<NT, EPT>), dim3(R, n_heads), dim3(NT), 0, st, R, S_max,
-                         cand_len, mask, a_rows, p_q, row_sel, row_k, status);
-    }
-    {
-      TimedLaunch t(HK_TK_VOTE_COUNT, st);
-      const int nw = S_max / 32;
-      hipLaunchKernelGGL(vote_count_kernel, dim3((nw + VC_NT - 1) / VC_NT, n_heads), dim3(VC_NT), 0,
-                         st, R, S_max, row_sel, votes);
-    }
-    return hipGetLastError();
-  }
-};
+// 512 threads and the fewest elements per thread that cover the row, or, past 512 * 64
+// slots, 1024 threads with 64 elements each
+template <typename... A>
+static hipError_t vote_topp_by_size(int S_max, A... a) {
+  if (S_max > BG_SLOTS_512) return run_vote_topp<1024, 64>(S_max, a...);
+  const int e = (S_max + 511) / 512;
+  if (e <= 1) return run_vote_topp<512, 1>(S_max, a...);
+  if (e <= 2) return run_vote_topp<512, 2>(S_max, a...);
+  if (e <= 4) return run_vote_topp<512, 4>(S_max, a...);
+  if (e <= 8) return run_vote_topp<512, 8>(S_max, a...);
+  if (e <= 16) return run_vote_topp<512, 16>(S_max, a...);
+  if (e <= 32) return run_vote_topp<512, 32>(S_max, a...);
+  return run_vote_topp<512, 64>(S_max, a...);
+}
 
 template <int NT, int EPT, bool RANK_C>
 static hipError_t run_budget_select(int n_heads, int S_max, const int32_t* cand_len, const uint16_t* mask,
@@ -1159,8 +1106,7 @@ using namespace hk;
 hipError_t hk_launch_vote_topp(int n_heads, int R, int S_max, const int32_t* cand_len,
                                const uint16_t* mask, const float* a_rows, int p_q, uint16_t* votes,
                                int32_t* row_k, uint32_t* row_sel, int32_t* status, hipStream_t st) {
-  return by_ept<VoteLaunch>(S_max, n_heads, R, S_max, cand_len, mask, a_rows, p_q, row_sel, row_k,
-                            status, votes, st);
+  return vote_topp_by_size(S_max, n_heads, R, cand_len, mask, a_rows, p_q, votes, row_k, row_sel, status, st);
 }
 
 hipError_t hk_launch_budget_plan(int n_heads, int max_pages, const int32_t* n_pages,
