@@ -101,7 +101,7 @@ __device__ __forceinline__ unsigned long long sw_uniform(unsigned long long x) {
   return ((unsigned long long)hi << 32) | lo;
 }
 
-// Chunks of a head to be worked on: those that can hold a candidate when `skip`, else all.
+// Chunks of a head to be worked on: those that can hold a candidate with SKIP, else all.
 // The others (a table wider than the row, or the dense tier) write no pieces, histogram or
 // keys, and nothing reads theirs: prep, chunk and bitmap leave them at once (but for the
 // zeros of c_out and of the bitmap), and pieces and histograms are summed over the live
@@ -110,9 +110,9 @@ __device__ __forceinline__ unsigned long long sw_uniform(unsigned long long x) {
 // skip: knowing the head's candidates first delays its loads by a memory round trip (8 heads
 // x 8192 slots: 51.2 us for score and selection, 52.4 with skipping).
 constexpr int SW_RESIDENT = 2048;              // 256-thread workgroups the chip holds at once
-__device__ __forceinline__ int sw_live(int h, int C, int S_max, const int32_t* __restrict__ cand_len,
-                                       int skip) {
-  return skip ? min(C, (min(cand_len[h], S_max) + SW_CH - 1) / SW_CH) : C;
+template <bool SKIP>
+__device__ __forceinline__ int sw_live(int h, int C, int S_max, const int32_t* __restrict__ cand_len) {
+  return SKIP ? min(C, (min(cand_len[h], S_max) + SW_CH - 1) / SW_CH) : C;
 }
 
 // The thread's four consecutive slots of half r of chunk c start at this slot.
@@ -153,14 +153,15 @@ __device__ __forceinline__ void sw_load8(const float* __restrict__ row, int c, i
   }
 }
 
+template <bool SKIP>
 __global__ __launch_bounds__(SW_NT) void sw_prep_kernel(
-    int S_max, int C, int skip, const int32_t* __restrict__ cand_len,
+    int S_max, int C, const int32_t* __restrict__ cand_len,
     const uint16_t* __restrict__ mask, int n_metrics, const float* __restrict__ x0, const float* __restrict__ x1,
     const float* __restrict__ T0, const float* __restrict__ T1, float2* __restrict__ part) {
   __shared__ float red[2][SW_NW];
   const int c = (int)blockIdx.x % C, h = (int)blockIdx.x / C, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  if (c >= sw_live(h, C, S_max, cand_len, skip)) return;
+  if (c >= sw_live<SKIP>(h, C, S_max, cand_len)) return;
   const uint32_t cb = sw_cand(h, c, S_max, cand_len, mask);
   for (int m = 0; m < n_metrics; ++m) {
     const float* Tp = (m == 0 ? T0 : T1);
@@ -191,9 +192,9 @@ __global__ __launch_bounds__(SW_NT) void sw_prep_kernel(
   }
 }
 
-template <bool CALIB>
+template <bool CALIB, bool SKIP>
 __global__ __launch_bounds__(SW_NT) void sw_chunk_kernel(
-    int S_max, int C, int skip, const int32_t* __restrict__ cand_len,
+    int S_max, int C, const int32_t* __restrict__ cand_len,
     const uint16_t* __restrict__ mask, int n_metrics, const float* __restrict__ x0, const float* __restrict__ x1,
     const float* __restrict__ T0, const float* __restrict__ T1, float w0, float w1,
     const float2* __restrict__ part, const float* __restrict__ c_in, float* __restrict__ c_out,
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(SW_NT) void sw_chunk_kernel(
   __shared__ float s_lse[2];
   const int c = (int)blockIdx.x % C, h = (int)blockIdx.x / C, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  const int live = sw_live(h, C, S_max, cand_len, skip);
+  const int live = sw_live<SKIP>(h, C, S_max, cand_len);
   if (c >= live) {
     if (CALIB && c_out)
 #pragma unroll
@@ -578,19 +579,20 @@ __device__ __forceinline__ SwFound sw_search(const unsigned long long (&bw1)[1],
 // FT threads: SW_FT, or SW_FS for rows of up to SW_SHORT slots in a launch of more heads than
 // CUs, whose list leaves LDS for a second workgroup on the CU (1024 heads in a 12288-slot
 // table: 41 us with one 1024-thread workgroup per CU).
-template <int FT>
+template <int FT, bool SKIP>
 __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(4, 8))) void sw_finish_kernel(
-    int S_max, int C_all, int skip, const int32_t* __restrict__ cand_len, int list_cap,
+    int S_max, int C_all, const int32_t* __restrict__ cand_len, int row_cap,
     const unsigned long long* __restrict__ hp, const uint16_t* __restrict__ ho,
     const uint32_t* __restrict__ sorted, int p_q, int k_min, int k_max, uint4* __restrict__ params,
     int32_t* __restrict__ k_out, float* __restrict__ sel_mass) {
   extern __shared__ __align__(16) unsigned char sw_dyn[];
   __shared__ SwSh sh;
   const int h = blockIdx.x, tid = threadIdx.x;
+  const int list_cap = FT == SW_FT ? SW_LIST : row_cap;
   uint32_t* list = reinterpret_cast<uint32_t*>(sw_dyn);
   unsigned long long* hw2 = reinterpret_cast<unsigned long long*>(sw_dyn + (size_t)list_cap * 4);
   uint32_t* hc2 = reinterpret_cast<uint32_t*>(sw_dyn + (size_t)list_cap * 4 + SW_B2 * 8);
-  const int C = sw_live(h, C_all, S_max, cand_len, skip);
+  const int C = sw_live<SKIP>(h, C_all, S_max, cand_len);
   // the halves of the level-1 sums, in the list's space before the list is used
   unsigned long long(*s_half)[SW_B1] = reinterpret_cast<unsigned long long(*)[SW_B1]>(sw_dyn);
   const unsigned long long* hprow = hp + (size_t)h * C_all * SW_B1;
@@ -764,15 +766,16 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(4, 8))) void
 }
 
 // One workgroup per (head, chunk): the chunk's words of the selection bitmap.
+template <bool SKIP>
 __global__ __launch_bounds__(SW_NT) void sw_bitmap_kernel(
-    int S_max, int C, int skip, const unsigned long long* __restrict__ hp,
+    int S_max, int C, const unsigned long long* __restrict__ hp,
     const uint16_t* __restrict__ ho, const uint32_t* __restrict__ sorted, const uint4* __restrict__ params,
     const int32_t* __restrict__ cand_len, uint32_t* __restrict__ sel_bits) {
   __shared__ uint32_t bits[SW_CH / 32];
   const int c = (int)blockIdx.x % C, h = (int)blockIdx.x / C, tid = threadIdx.x;
   if (tid < SW_CH / 32) bits[tid] = 0u;
   const uint4 p = params[h];
-  const bool live = c < sw_live(h, C, S_max, cand_len, skip);
+  const bool live = c < sw_live<SKIP>(h, C, S_max, cand_len);
   const uint32_t v = p.x, tie_from = p.y, d1 = p.z;
   __syncthreads();
   if (live && v != SW_NONE) {
@@ -830,12 +833,13 @@ using namespace hk;
 
 size_t hk_select_wide_ws(int n_heads, int S_max) { return sw_ws(n_heads, S_max).total; }
 
-hipError_t hk_launch_select_wide(int n_heads, int S_max, const int32_t* cand_len,
-                                 const uint16_t* mask, int n_metrics, const float* x0,
-                                 const float* x1, const float* T0, const float* T1, float w0,
-                                 float w1, const float* c_in, int p_q, int k_min, int k_max,
-                                 float* c_out, float* lse_out, uint32_t* sel_bits, int32_t* k_out,
-                                 float* sel_mass, int32_t* status, void* ws, hipStream_t st) {
+template <bool SKIP>
+static hipError_t launch_select_wide(int n_heads, int S_max, const int32_t* cand_len,
+                                     const uint16_t* mask, int n_metrics, const float* x0,
+                                     const float* x1, const float* T0, const float* T1, float w0,
+                                     float w1, const float* c_in, int p_q, int k_min, int k_max,
+                                     float* c_out, float* lse_out, uint32_t* sel_bits, int32_t* k_out,
+                                     float* sel_mass, int32_t* status, void* ws, hipStream_t st) {
   const SwWs w = sw_ws(n_heads, S_max);
   char* base = static_cast<char*>(ws);
   float2* part = reinterpret_cast<float2*>(base + w.part);
@@ -845,33 +849,44 @@ hipError_t hk_launch_select_wide(int n_heads, int S_max, const int32_t* cand_len
   uint4* params = reinterpret_cast<uint4*>(base + w.params);
   const int C = (S_max + SW_CH - 1) / SW_CH;
   const dim3 chunks(C * n_heads), block(SW_NT);
-  const int skip = (long long)C * n_heads > SW_RESIDENT;
   TimedLaunch t(n_metrics > 0 ? HK_TK_CALIB_TOPP : HK_TK_TOPP, st);
   if (n_metrics > 0) {
-    hipLaunchKernelGGL(sw_prep_kernel, chunks, block, 0, st, S_max, C, skip, cand_len, mask, n_metrics,
+    hipLaunchKernelGGL(sw_prep_kernel<SKIP>, chunks, block, 0, st, S_max, C, cand_len, mask, n_metrics,
                        x0, x1, T0, T1, part);
-    hipLaunchKernelGGL(sw_chunk_kernel<true>, chunks, block, 0, st, S_max, C, skip, cand_len, mask,
+    hipLaunchKernelGGL((sw_chunk_kernel<true, SKIP>), chunks, block, 0, st, S_max, C, cand_len, mask,
                        n_metrics, x0, x1, T0, T1, w0, w1, part, c_in, c_out, lse_out, hp, ho,
                        sorted, status);
   } else {
-    hipLaunchKernelGGL(sw_chunk_kernel<false>, chunks, block, 0, st, S_max, C, skip, cand_len, mask, 0,
+    hipLaunchKernelGGL((sw_chunk_kernel<false, SKIP>), chunks, block, 0, st, S_max, C, cand_len, mask, 0,
                        x0, x1, T0, T1, w0, w1, part, c_in, c_out, lse_out, hp, ho, sorted, status);
   }
   // the finishing workgroup's list never holds more keys than the row has slots: rows of up to
   // SW_SHORT slots leave LDS for a second workgroup on the CU
-  const int list_cap = std::min(std::max((S_max + 63) & ~63, SW_LIST_MIN), SW_LIST);
   const auto lds_of = [](int cap) { return (size_t)cap * 4 + SW_B2 * 12; };
-  const size_t lds = lds_of(list_cap);
   if (S_max <= SW_SHORT && n_heads > 256) {
-    allow_dynamic_lds<sw_finish_kernel<SW_FS>>(lds_of(SW_SHORT));     // raised once: the most it takes
-    hipLaunchKernelGGL(sw_finish_kernel<SW_FS>, dim3(n_heads), dim3(SW_FS), lds, st, S_max, C, skip, cand_len,
-                       list_cap, hp, ho, sorted, p_q, k_min, k_max, params, k_out, sel_mass);
+    const int cap = std::max((S_max + 63) & ~63, SW_LIST_MIN);
+    allow_dynamic_lds<sw_finish_kernel<SW_FS, SKIP>>(lds_of(SW_SHORT));     // once: the most it takes
+    hipLaunchKernelGGL((sw_finish_kernel<SW_FS, SKIP>), dim3(n_heads), dim3(SW_FS), lds_of(cap), st, S_max, C,
+                       cand_len, cap, hp, ho, sorted, p_q, k_min, k_max, params, k_out, sel_mass);
   } else {
-    allow_dynamic_lds<sw_finish_kernel<SW_FT>>(lds_of(SW_LIST));
-    hipLaunchKernelGGL(sw_finish_kernel<SW_FT>, dim3(n_heads), dim3(SW_FT), lds, st, S_max, C, skip, cand_len,
-                       list_cap, hp, ho, sorted, p_q, k_min, k_max, params, k_out, sel_mass);
+    allow_dynamic_lds<sw_finish_kernel<SW_FT, SKIP>>(lds_of(SW_LIST));
+    hipLaunchKernelGGL((sw_finish_kernel<SW_FT, SKIP>), dim3(n_heads), dim3(SW_FT), lds_of(SW_LIST), st, S_max, C,
+                       cand_len, SW_LIST, hp, ho, sorted, p_q, k_min, k_max, params, k_out, sel_mass);
   }
-  hipLaunchKernelGGL(sw_bitmap_kernel, chunks, block, 0, st, S_max, C, skip, hp, ho, sorted, params,
+  hipLaunchKernelGGL(sw_bitmap_kernel<SKIP>, chunks, block, 0, st, S_max, C, hp, ho, sorted, params,
                      cand_len, sel_bits);
   return hipGetLastError();
+}
+
+hipError_t hk_launch_select_wide(int n_heads, int S_max, const int32_t* cand_len,
+                                 const uint16_t* mask, int n_metrics, const float* x0,
+                                 const float* x1, const float* T0, const float* T1, float w0,
+                                 float w1, const float* c_in, int p_q, int k_min, int k_max,
+                                 float* c_out, float* lse_out, uint32_t* sel_bits, int32_t* k_out,
+                                 float* sel_mass, int32_t* status, void* ws, hipStream_t st) {
+  // a constant of the kernels: as an argument it cost launches that skip nothing 0.3 us of 20
+  const bool skip = (long long)((S_max + SW_CH - 1) / SW_CH) * n_heads > SW_RESIDENT;
+  return (skip ? launch_select_wide<true> : launch_select_wide<false>)(
+      n_heads, S_max, cand_len, mask, n_metrics, x0, x1, T0, T1, w0, w1, c_in, p_q, k_min, k_max, c_out,
+      lse_out, sel_bits, k_out, sel_mass, status, ws, st);
 }
