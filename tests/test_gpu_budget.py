@@ -199,6 +199,31 @@ def test_budget_plan(name):
     assert O.REWRITE in seen and O.KEEP in seen
 
 
+# rows of odd and even page counts on both sides of the 2048 pages a workgroup counts at a time,
+# with bits past a row's last page that are not its own (metadata only: no page is read)
+@pytest.mark.parametrize("max_pages", [2, 2050, 4104])
+def test_budget_plan_long_rows(max_pages):
+    import paper_2606_28831_amd as hk
+    rng = np.random.default_rng(max_pages)
+    ends = [0, 1, 2, 3, 63, 511, 512, 2047, 2048, 2049, 2050, 4095, 4096, 4097, max_pages - 1, max_pages]
+    n = np.array([e for e in ends if e <= max_pages], np.int32)
+    H = len(n)
+    mask = rng.integers(0, 1 << 16, (H, max_pages)).astype(np.int64)
+    pool = torch.zeros(1, 16, 64, dtype=torch.bfloat16, device=DEV)
+    kv = hk.PagedKV(pool, pool, torch.zeros(H, max_pages, dtype=torch.int32, device=DEV),
+                    torch.tensor(mask.astype(np.uint16).view(np.int16), device=DEV), torch.tensor(n, device=DEV))
+    mode, cap = (torch.empty(H, dtype=torch.int32, device=DEV) for _ in "mc")
+    for h in range(H):                                   # each row's own count and one below it
+        valid = int(sum(bin(int(m)).count("1") for m in mask[h, :n[h]]))
+        for L_lower in {valid, max(0, valid - 1)}:
+            L_upper = max(L_lower, 16 * int(n[h]))
+            hk.hk_budget_plan(hk.dims(H, 1, 1, 64), kv, 48, L_lower, L_upper, mode, cap)
+            torch.cuda.synchronize()
+            for g in range(H):
+                ref = O.budget_plan_head(int(n[g]), mask[g], 48, L_lower, L_upper)
+                assert (int(mode[g]), int(cap[g])) == ref, (max_pages, L_lower, int(n[g]))
+
+
 # ---------------------------------------------------------------- budget selection
 # both sides of the sizes where a workgroup changes its threads or their elements
 @pytest.mark.parametrize("S", [64, 1024, 2048, 4096, 4128, 8192, 8224, 16384, 16416, 32768, 33792, 65536])

@@ -202,16 +202,17 @@ def test_decode_bf16_extreme_scores(G):
     cfg = dict(L=1, B=H, Hq=G, Hkv=1, D=D, N=pages * 16, dtype="bf16", W=8, seed=53, recipe="normal")
     w = WL.make_workload(cfg, DEV, max_pages=pages)
     n = pages * 16
+    gen = torch.Generator(device=DEV).manual_seed(53)
     step = torch.arange(n, device=DEV, dtype=torch.float32)
     gain = torch.stack([step * 0.2, (n - step) * 0.2, torch.where(step % 37 == 0, 60.0, -60.0), step * 0])
     u = torch.ones(D, device=DEV)
     for h in range(H):
-        k = (torch.randn(n, D, device=DEV) * 0.1 + gain[h][:, None] * u / D ** 0.5).to(torch.bfloat16)
+        k = (torch.randn(n, D, generator=gen, device=DEV) * 0.1 + gain[h][:, None] * u / D ** 0.5).to(torch.bfloat16)
         w.k_pool[w.page_table[h].long()] = k.view(pages, 16, D)
     w.v_pool[w.page_table[3, 3].long(), 5, 7] = float("inf")      # a key of every weight but 0
     kv = hk.PagedKV(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
     d = hk.dims(H, G, 1, D)
-    q = (torch.randn(H, G, D, device=DEV) * 0.1 + u).to(torch.bfloat16)
+    q = (torch.randn(H, G, D, generator=gen, device=DEV) * 0.1 + u).to(torch.bfloat16)
     o, lse = torch.empty(H, G, D, device=DEV), torch.empty(H, G, device=DEV)
     hk.hk_decode_attn(d, q, kv, 1 / math.sqrt(D), o, lse, hk.workspace(hk.OP_DECODE, d, w.max_pages, DEV))
     torch.cuda.synchronize()
