@@ -518,16 +518,21 @@ __global__ __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(3, 4))) 
 
 // NW waves per query head merge its split states (App. F).  Lanes hold two output columns
 // each, and a group of D / 2 lanes takes every NG-th split, U of them in flight at once, so
-// the chain of dependent loads is n_split / (NG * U) long.  Every wave reads all (m, l) itself (64 splits per load) for the running
-// maximum M and the rescaled sum L; a split's own factor exp2(m - M) comes from the m loaded
-// beside its outputs.  The first batch of loads -- page count, states and outputs -- is issued
-// before the number of splits that held pages is known; the states of the others are dropped
-// unread (their memory holds an earlier call's values).  Launches of at most 8 splits take
-// one wave per query head, which then has every split in flight; more splits take four
-// waves.  Bound by the latency of two or three dependent loads: 16 heads x 7 query heads x
-// 128 splits 45.6 -> 5.5 us against one workgroup per KV head with four loads in flight per
-// thread, 8 heads x 4 x 48 splits 5.7 -> 3.2 us, 512 heads x 4 x 6 splits 6.3 -> 5.3 us.
+// the chain of dependent loads is n_split / (NG * U) long.  Every wave reads all (m, l) itself
+// (64 splits per load) for the running maximum M and the rescaled sum L; a split's own factor
+// exp2(m - M) comes from the m loaded beside its outputs.  The first batch of loads -- page
+// count, states and outputs -- is issued before the number of splits that held pages is
+// known; the states of the others are dropped unread (their memory holds an earlier call's
+// values).  Launches of at most 8 splits take one wave per query head, which then has every
+// split in flight; more splits take four waves.  Up to 32 splits of more than MRG_MANY query
+// heads stay at one: those waves fill the chip, and four times as many only queue and load
+// dead splits (1024 heads x 4 x 12 splits 10.2 us with four waves, 6.5 with one, 6.8 with one
+// workgroup per KV head; 488 x 4 x 16 6.3, 4.8 and 6.7).  Bound by the latency of two or three
+// dependent loads: 16 heads x 7 query heads x 128 splits 45.6 -> 5.5 us against one workgroup
+// per KV head with four loads in flight per thread, 16 x 4 x 48 splits 11.3 -> 4.0 us, 512 x 4 x 6
+// splits 4.9 -> 3.7 us over a whole decode loop.
 constexpr int MRG_NT = 256;
+constexpr int MRG_MANY = 1024;               // query heads that fill the chip with one wave each
 template <int D, int NW, int U>
 __global__ __launch_bounds__(MRG_NT) void decode_merge_kernel(const float* __restrict__ part,
                                                               const int32_t* __restrict__ n_pages_arr,
@@ -815,11 +820,13 @@ hipError_t hk_launch_decode(int NS, int Hq, int Hkv, int D, const void* q, const
 #define HK_MERGE(D_, NW_, U_)                                                                      \
   hipLaunchKernelGGL((decode_merge_kernel<D_, NW_, U_>), dim3((n_q * NW_ + 3) / 4), dim3(MRG_NT), 0, \
                      st, part, kv->n_pages, kv->max_pages, n_split, pps, n_q, G, Hq, Hkv, o, lse)
+  const bool one_wave = n_split <= 8 || (n_q > MRG_MANY && n_split <= 32);
   if (D == 128) {
-    if (n_split <= 8) HK_MERGE(128, 1, 8);
+    if (one_wave) HK_MERGE(128, 1, 8);
     else HK_MERGE(128, 4, 8);
   } else {
     if (n_split <= 8) HK_MERGE(64, 1, 4);
+    else if (one_wave) HK_MERGE(64, 1, 8);
     else HK_MERGE(64, 4, 8);
   }
 #undef HK_MERGE

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
-def _decode_against_oracle(cfg, lens, max_pages, hole_prob=0.1, n_split=None, q_scale=2.0):
+def _decode_against_oracle(cfg, lens, max_pages, hole_prob=0.1, n_split=None, q_scale=2.0, heads=None):
     import paper_2606_28831_amd as hk
     w = WL.make_workload(cfg, DEV, hole_prob=hole_prob, head_lens=lens, max_pages=max_pages)
     kv = hk.PagedKV(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
@@ -31,10 +31,10 @@ def _decode_against_oracle(cfg, lens, max_pages, hole_prob=0.1, n_split=None, q_
     ws.fill_(255)                      # NaN in every float an idle split leaves unwritten
     hk.hk_decode_attn(d, q, kv, scale, o, lse, ws)
     torch.cuda.synchronize()
-    host = HostCache(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages)
+    host = HostCache(w.k_pool, w.v_pool, w.page_table, w.page_mask, w.n_pages, heads=heads)
     qn, on, ln = np64(q), np64(o), np64(lse)
     G, rtol = cfg["Hq"] // cfg["Hkv"], RTOL[cfg["dtype"]]
-    for h in range(w.n_heads):
+    for h in range(w.n_heads) if heads is None else heads:
         s, kvh = divmod(h, cfg["Hkv"])
         K, valid = host.head(h)
         V, _ = host.head_v(h)
@@ -51,6 +51,18 @@ def _decode_against_oracle(cfg, lens, max_pages, hole_prob=0.1, n_split=None, q_
 def test_decode_merge_shapes(D, G, dtype, pages):
     cfg = dict(L=1, B=3, Hq=G, Hkv=1, D=D, N=pages * 16, dtype=dtype, W=8, seed=41, recipe="normal")
     _decode_against_oracle(cfg, [pages * 16, 0, pages * 8 + 5], pages, n_split=-(-pages // 16))
+
+
+# more query heads than the merge gives four waves each: one wave at 9 to 32 splits, four above
+@pytest.mark.parametrize("D,dtype,pages", [(128, "bf16", 1156), (64, "f32", 1156), (64, "bf16", 4096),
+                                           (128, "bf16", 4228)])
+def test_decode_merge_many_heads(D, dtype, pages):
+    H = 1030
+    cfg = dict(L=1, B=H, Hq=1, Hkv=1, D=D, N=pages * 16, dtype=dtype, W=8, seed=71, recipe="normal")
+    lens = [(i * 37) % 301 for i in range(H)]            # some of no page at all
+    lens[5], lens[77], lens[500], lens[H - 1] = 18000, 16 * pages, 4100, 9 * 128 * 16 + 1
+    heads = [0, 1, 5, 77, 255, 500, 511, 512, H - 2, H - 1]
+    _decode_against_oracle(cfg, lens, pages, n_split=-(-pages // 128), heads=heads)
 
 
 # the second pass's chunks of 16 pages up to 128: few rows take short ones; rows that end before,
