@@ -211,12 +211,12 @@ hk_status hk_calibrate_topp(int32_t n_heads, int32_t S_max, const int32_t* cand_
                             float* sel_mass_out, int32_t* status, hipStream_t stream);
 
 /* ------------------------------------------------------------------ a2 + a3, wide
- * hk_topp_select and hk_calibrate_topp with every head spread over ceil(S_max / 4096)
+ * hk_topp_select and hk_calibrate_topp with every head spread over ceil(S_max / 2048)
  * workgroups (Sec. 3.2, Problem 1 and Solution 2): for caches longer than 32768 slots, and
  * so that a batch of few heads still fills the chip.  The Top-p rule is the one stated for
  * hk_topp_select, in the same exact integers, so for the same c the selection, k_out and
  * sel_mass_out are those hk_topp_select writes, bit for bit.  hk_calibrate_topp_ws
- * assembles each head's log-sum-exp from 4096-slot pieces: its c_out and lse_out agree
+ * assembles each head's log-sum-exp from 2048-slot pieces: its c_out and lse_out agree
  * with hk_calibrate's to fp32 rounding, and its selection is the exact Top-p of the c it
  * computed (which it writes to c_out when given).
  * Arguments as for hk_topp_select / hk_calibrate_topp, plus

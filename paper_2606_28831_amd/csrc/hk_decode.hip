@@ -258,9 +258,9 @@ __global__ __launch_bounds__(DEC_NT) void decode_split_f32_kernel(
 // power of two.  Error of o against 64 bits, VALU form -> this: 1.77 -> 1.53e-7 (rows of 2000),
 // 2.41 -> 1.74e-7 (8192), 2.10 -> 1.91e-7 (23k to 33k), 2.31 -> 2.14e-7 (33k to 66k).
 // Bound by HBM reads.  The VALU form (two pages of prefetch, fdot2 and per-head fma) was
-// bound by issue from 7 heads on: 16 heads x 7 x 28k tokens 74 -> 43 us (with the merge),
-// 512 x 8 x 3000 218 -> 161, 512 x 4 x 8192 378 -> 370 (5.8 TB/s), 512 x 4 x 800-5600 172 -> 164,
-// 512 x 1 x 8192 unchanged at 359.
+// bound by issue from 7 heads on: 512 heads x 8 x 3000 tokens 218 -> 161 us, 512 x 4 x 8192 378 ->
+// 370 (5.8 TB/s), 512 x 4 x 800-5600 172 -> 164, 512 x 1 x 8192 unchanged at 359; 16 x 7 x 23k to 33k
+// 80 -> 56, both with the merge as it is.
 constexpr float DEC_SLACK = 16.f;
 constexpr int DEC_GMAX = 8;
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
