@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "hk_internal.h"
+#include "hk_turn.h"
 
 namespace hk {
 
@@ -270,7 +271,7 @@ __global__ __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(3, 4))) 
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_pool, const uint16_t* __restrict__ v_pool,
     const int32_t* __restrict__ table, const uint16_t* __restrict__ masks,
     const int32_t* __restrict__ n_pages_arr, int G, int Hq, int Hkv, int max_pages, float c2,
-    float* __restrict__ part, int n_split, int pps) {
+    float* __restrict__ part, int n_split, int pps, uint32_t heads_first) {
   constexpr int KS = D / 32;                // MFMA steps over the head dimension
   constexpr int VE = D / 16;                // dims of a V piece
   constexpr int VW = VE / 2;                // 32-bit words of a V piece
@@ -280,7 +281,11 @@ __global__ __launch_bounds__(DEC_NT) __attribute__((amdgpu_waves_per_eu(3, 4))) 
   __shared__ int32_t s_pid[DEC_PPS];
   __shared__ uint16_t s_pm[DEC_PPS];
 
-  const int h = blockIdx.y, split = blockIdx.x;
+  int h = blockIdx.y, split = blockIdx.x;
+  if (heads_first) {
+    split = h;
+    h = head_of(blockIdx.x, split, (int)gridDim.x, heads_first);
+  }
   const int s = h / Hkv, kv = h % Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = min(n_pages_arr[h], max_pages);
@@ -747,11 +752,11 @@ __global__ __launch_bounds__(AP_NT) void append_write_kernel(
 
 template <int D>
 static void launch_split(int G, dim3 grid, hipStream_t st, const void* q, const hk_paged_kv* kv, int Hq,
-                         int Hkv, float c2, float* part, int n_split, int pps) {
+                         int Hkv, float c2, float* part, int n_split, int pps, uint32_t heads_first) {
   hipLaunchKernelGGL(decode_split_kernel<D>, grid, dim3(DEC_NT), 0, st, static_cast<const uint16_t*>(q),
                      static_cast<const uint16_t*>(kv->k_pool), static_cast<const uint16_t*>(kv->v_pool),
                      kv->page_table, kv->page_mask, kv->n_pages, G, Hq, Hkv, kv->max_pages, c2, part,
-                     n_split, pps);
+                     n_split, pps, heads_first);
 }
 
 template <int D, int G>
@@ -805,13 +810,24 @@ hipError_t hk_launch_decode(int NS, int Hq, int Hkv, int D, const void* q, const
   hk_decode_split_plan(n_heads, kv->max_pages, &pps, &n_split);
   const float c2 = sm_scale * kLog2e;
   float* part = static_cast<float*>(ws);
-  dim3 grid(n_split, n_heads);
   const bool bf = kv->dtype == HK_BF16;
+  // One or two query heads of a bf16 cache: the launch runs over the heads first, so that the
+  // splits past the rows' ends come last.  With a head's splits in turn they lie between the
+  // others, and as workgroups go to the eight dies and their CUs in turn, the first 3 splits of
+  // 16 all fall to three dies.  There the matrix-core kernel was slower than the VALU form had
+  // been: 512 heads of 641 tokens in a 32768-token table, G 1, 70 us (VALU form), 107, heads first
+  // 32; G 2 87, 109, 33; 64 heads of 640 in 12288 at G 1 16.5, 21.9, 11.2.  From 4 query heads on it
+  // was faster in that order too, and where most splits hold pages that order is better by up
+  // to 4% (16 heads x 7 x 23k to 33k tokens 55.6 us, heads first 57.1).  The heads are turned
+  // by the split, or a head's splits would all meet on one die.
+  const bool by_heads = bf && G <= 2 && n_split <= 65535;
+  const uint32_t heads_first = by_heads ? turn_magic(n_heads) : 0u;
+  const dim3 grid(by_heads ? n_heads : n_split, by_heads ? n_split : n_heads);
   if (!hk_decode_supports_group(G)) return hipErrorInvalidValue;
   {
     TimedLaunch t(timed ? HK_TK_DECODE_SPLIT : -1, st);
-    if (bf && D == 128) launch_split<128>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps);
-    else if (bf) launch_split<64>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps);
+    if (bf && D == 128) launch_split<128>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps, heads_first);
+    else if (bf) launch_split<64>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps, heads_first);
     else if (D == 128) launch_split_f32_g<128>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps);
     else launch_split_f32_g<64>(G, grid, st, q, kv, Hq, Hkv, c2, part, n_split, pps);
   }
